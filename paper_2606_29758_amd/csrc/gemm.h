@@ -29,24 +29,33 @@
 //
 // Pipeline: K advances in steps of 32 (one MFMA depth) through a ring of
 // kStages = 4 LDS stages of 40 KB, filled by global_load_lds_dwordx4 (no
-// staging registers).  Step kt runs 12 groups of 8 MFMAs (row block g times
-// the 8 column blocks), with one work-group barrier in the middle of the step
-// (before group 6) that waits until step kt+1's stage has landed:
-//   * groups 0..5 read this step's A blocks 6..11 (A operands are
+// staging registers).  Step kt runs 96 MFMAs (12 row blocks times 8 column
+// blocks), with one work-group barrier in the middle of the step (before row
+// block 6) that waits until step kt+1's stage has landed:
+//   * the first half reads this step's A blocks 6..11 (A operands are
 //     single-buffered: a block's register is refilled only after its MFMAs)
-//     and issue the 4 B-panel loads of step kt+3;
-//   * groups 6..11 read step kt+1's A blocks 0..5 and its 8 B blocks (B is
-//     double-buffered) and issue the 6 A-panel loads of step kt+4 into the
+//     and issues the 4 B-panel loads of step kt+3;
+//   * the second half reads step kt+1's A blocks 0..5 and its 8 B blocks (B is
+//     double-buffered) and issues the 6 A-panel loads of step kt+4 into the
 //     stage this step used (every read of it was done before the barrier).
 // A stage is refilled half a step after its last read, so a load has 1.75 to
 // 2.5 steps to land before the barrier that needs it (a barrier at the end of
 // the step gives 1.1 to 1.9 with four stages); measured 3-5% faster.
-// A group's LDS reads go out after its MFMAs (they feed later groups), except
-// that the reads of groups 5 and 11 are issued by groups 4 and 10, ahead of
-// their MFMAs: the two full LDS waits of a step (at the barrier, and before
-// the next step's first MFMAs, which need all eight B blocks) then find their
-// last reads sixteen MFMAs old instead of just issued (-1% per loss call).
-// Each group is fenced with sched_barrier so the compiler keeps the interleave.
+// What bounds the loop is issue: each SIMD runs one wave, an MFMA occupies the
+// matrix core for 16 clocks and the wave issues about one instruction per 4, so
+// three other instructions hide behind an MFMA and every further one before the
+// next MFMA leaves the matrix core idle.  So at most one LDS read or load goes
+// out after each MFMA, the loads take a scalar base and immediate offsets (no
+// vector address arithmetic, one LDS base per operand), and the scalar updates
+// have slots of their own; sched_barriers keep the compiler to that order.
+// With the same reads and loads in clumps of 2 to 7 (and their addresses
+// computed per load) after every eighth MFMA, the matrix cores were busy 74%
+// (forward), 67, 69 and 76% (logit gradient, dW, dH) of the cycles; now 83, 75,
+// 77 and 86%, of which the chip gives part back (1.81 -> 1.71 GHz, the power
+// limit): 18.81 -> 17.81, 11.88 -> 11.20, 11.77 -> 11.26 and 11.21 -> 10.49 ms at
+// 24,576 tokens, d = 3584, V = 152064.  The reads of the second half go out back
+// to back, before the loads: spread among them 0.5-1.8% slower (the two meet in
+// the LDS), two reads per MFMA 2% slower, loads back to back 2% slower.
 // LDS rows are 64 bytes; the four 16-byte chunks of row r are stored XOR-ed
 // with ((r >> 1) ^ (r >> 2)) & 3 (bank-conflict free for the 16-row operand
 // reads, period 16 rows).
@@ -333,6 +342,15 @@ struct Const {
   static constexpr int value = N;
 };
 
+// f(Const<0>{}), ..., f(Const<N - 1>{}).
+template <int N, class F>
+__device__ __forceinline__ void repeat(F&& f) {
+  if constexpr (N > 0) {
+    repeat<N - 1>(f);
+    f(Const<N - 1>{});
+  }
+}
+
 typedef __attribute__((address_space(3))) void lds_void;
 
 // c += a * b on one 16 x 16 x 32 bf16 block, accumulating in place (AGPRs or
@@ -432,106 +450,89 @@ void gemm_nt_kernel(GemmShape g, Epi epi) {
     for (int j = 0; j < kBlocksN; ++j) acc.v[i][j] = f32x4{};
 
 
-  auto read_a = [&](int stage, int i) -> bf16x8 {
-    return __builtin_bit_cast(bf16x8,
-                              *reinterpret_cast<const u32x4*>(lds + stage * kLdsStage + rdA + i * 16 * kLdsRow));
+  // Loads go through a scalar base that advances one K step at a time (held at
+  // the last step once it is reached: every step issues the same count, and the
+  // surplus loads are in bounds and never consumed), one 32-bit lane offset, and
+  // immediate offsets that apply to the global and the LDS address alike.
+  const uint32_t lds_a = wave * (kTileM / 4) * kLdsRow, lds_b = kLdsA + wave * (kTileN / 4) * kLdsRow;
+  uint32_t voff = lane_off;
+  auto load_a = [&](const unsigned char* p, uint32_t stage, auto qc) {
+    constexpr int q = decltype(qc)::value, hi = q / 4 * 4 * 16 * kLdsRow;
+    __builtin_amdgcn_global_load_lds(p + hi + voff, (lds_void*)(lds + stage + lds_a + hi), 16, q % 4 * 16 * kLdsRow, 0);
   };
-  auto read_b = [&](int stage, int j) -> bf16x8 {
-    return __builtin_bit_cast(bf16x8,
-                              *reinterpret_cast<const u32x4*>(lds + stage * kLdsStage + rdB + j * 16 * kLdsRow));
+  auto load_b = [&](const unsigned char* p, uint32_t stage, auto qc) {
+    constexpr int q = decltype(qc)::value;
+    __builtin_amdgcn_global_load_lds(p + voff, (lds_void*)(lds + stage + lds_b), 16, q * 16 * kLdsRow, 0);
   };
-  // Load q (0..9) of step kt into `stage`; steps past the last reload the last
-  // one (in bounds, never consumed), so every step issues the same count.
-  auto issue_load = [&](int kt, int stage, int q) {
-    const int64_t kk = max(min(kt, nk - 1), 0);
-    if (q < kLoadsA) {
-      __builtin_amdgcn_global_load_lds(
-          gA + kk * kstep_a + q * 16 * kLdsRow + lane_off,
-          (lds_void*)(lds + stage * kLdsStage + (wave * (kTileM / 4) + q * 16) * kLdsRow), 16, 0, 0);
-    } else {
-      __builtin_amdgcn_global_load_lds(
-          gB + kk * kstep_b + (q - kLoadsA) * 16 * kLdsRow + lane_off,
-          (lds_void*)(lds + stage * kLdsStage + kLdsA + (wave * (kTileN / 4) + (q - kLoadsA) * 16) * kLdsRow), 16,
-          0, 0);
-    }
+  // an MFMA operand block: 16 rows of 64 bytes from LDS offset `at` on
+  auto read = [&](uint32_t at, int blk) -> bf16x8 {
+    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(lds + at + blk * 16 * kLdsRow));
   };
 
-  // Group g of step kt: (the mid-step barrier before group 6,) 8 MFMAs of row
-  // block g on B slot s, then its LDS reads and global->LDS loads (groups 4
-  // and 10: the reads of g and g + 1 first, then the MFMAs).  Loads of step s
-  // go out in groups 6..11 of step s-4 (A) and 0..3 of step s-3 (B); at the
-  // barrier of step kt, step kt+1's loads must have landed, and the 20 issued
-  // after them (steps kt+2, kt+3) may still be in flight.
-  auto group = [&](auto slot, int kt, int cur, int nxt, auto gq) {
-    constexpr int s = decltype(slot)::value, gi = decltype(gq)::value;
-    if constexpr (gi == kBlocksM / 2) stage_barrier<2 * (kLoadsA + kLoadsB)>();
-    // the LDS reads that belong to group g (none feeds group g's own MFMAs):
-    // groups 0..5 read this step's A blocks 6..11; groups 6..11 the next
-    // step's A blocks 0..5 and its B blocks 2, 2, 1, 1, 1, 1
-    auto reads = [&](auto gr) {
-      constexpr int g = decltype(gr)::value;
-      if constexpr (g < kBlocksM / 2) {
-        fa[g + 6] = read_a(cur, g + 6);
-      } else {
-        fa[g - 6] = read_a(nxt, g - 6);
-        if constexpr (g == 6) {
-          fb[1 - s][0] = read_b(nxt, 0);
-          fb[1 - s][1] = read_b(nxt, 1);
-        } else if constexpr (g == 7) {
-          fb[1 - s][2] = read_b(nxt, 2);
-          fb[1 - s][3] = read_b(nxt, 3);
-        } else {
-          fb[1 - s][g - 4] = read_b(nxt, g - 4);
-        }
-      }
-    };
-    constexpr bool early = gi == kBlocksM / 2 - 2 || gi == kBlocksM - 2;   // groups 4 and 10
-    constexpr bool none = gi == kBlocksM / 2 - 1 || gi == kBlocksM - 1;    // groups 5 and 11
-    if constexpr (early) {
-      reads(Const<gi>{});
-      reads(Const<gi + 1>{});
-    }
-#pragma unroll
-    for (int j = 0; j < kBlocksN; ++j) {
-      if constexpr (gi < kBlocksAgpr) mfma_agpr(acc.a[gi][j], fa[gi], fb[s][j]);
-      else mfma_vgpr(acc.v[gi - kBlocksAgpr][j], fa[gi], fb[s][j]);
-    }
-    if constexpr (!early && !none) reads(Const<gi>{});
-    if constexpr (gi < kBlocksM / 2) {
-      if constexpr (gi < kLoadsB) issue_load(kt + 3, (kt + 3) % kStages, kLoadsA + gi);
-    } else {
-      issue_load(kt + 4, cur, gi - 6);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  };
+  // One K step kt: 96 MFMAs (row block g = i / 8, column block i % 8), at most
+  // one LDS read or load after each.  `cur`, `nxt`, `prv`: byte offsets of the
+  // stages of steps kt, kt+1 and kt-1 (= kt+3); pA and pB point at steps kt+4
+  // and kt+3; va: LDS offset of this step's A blocks, vn and vb those of the
+  // next step's A and B blocks.
+  uint32_t cur = 0, nxt = kLdsStage, prv = (kStages - 1) * kLdsStage;
+  uint32_t va = rdA, vn = rdA + kLdsStage, vb = rdB + kLdsStage;
+  const unsigned char *pA = gA, *pB = gB;
+  const uint32_t inc_a = (uint32_t)kstep_a, inc_b = (uint32_t)kstep_b;
   auto step = [&](auto slot, int kt) {
-    const int cur = kt % kStages, nxt = (kt + 1) % kStages;
-    group(slot, kt, cur, nxt, Const<0>{}); group(slot, kt, cur, nxt, Const<1>{});
-    group(slot, kt, cur, nxt, Const<2>{}); group(slot, kt, cur, nxt, Const<3>{});
-    group(slot, kt, cur, nxt, Const<4>{}); group(slot, kt, cur, nxt, Const<5>{});
-    group(slot, kt, cur, nxt, Const<6>{}); group(slot, kt, cur, nxt, Const<7>{});
-    group(slot, kt, cur, nxt, Const<8>{}); group(slot, kt, cur, nxt, Const<9>{});
-    group(slot, kt, cur, nxt, Const<10>{}); group(slot, kt, cur, nxt, Const<11>{});
+    constexpr int s = decltype(slot)::value;
+    asm volatile("" : "+v"(voff));   // keep the offset 32 bits wide: scalar base + vector offset addressing
+    auto mfma = [&](auto ic) {
+      constexpr int i = decltype(ic)::value, g = i / kBlocksN, j = i % kBlocksN;
+      if constexpr (i == kBlocksM * kBlocksN / 2) stage_barrier<2 * (kLoadsA + kLoadsB)>();
+      if constexpr (g < kBlocksAgpr) mfma_agpr(acc.a[g][j], fa[g], fb[s][j]);
+      else mfma_vgpr(acc.v[g - kBlocksAgpr][j], fa[g], fb[s][j]);
+      // first half: the B panel of step kt+3 and, between its loads, this
+      // step's A blocks 6..11
+      if constexpr (i % 6 == 1 && i / 6 < kLoadsB) load_b(pB, prv, Const<i / 6>{});
+      if constexpr (i % 6 == 4 && i / 6 < kBlocksM / 2) fa[6 + i / 6] = read(va, 6 + i / 6);
+      if constexpr (i == 38) pB += kt + 4 < nk ? inc_b : 0;
+      if constexpr (i == 41) vn = rdA + nxt;
+      if constexpr (i == 43) vb = rdB + nxt;
+      // second half: the next step's B blocks and A blocks 0..5 (the operands of
+      // its first MFMAs first), then the A panel of step kt+4
+      if constexpr (i >= 48 && i < 62) {
+        constexpr int k = i - 48;
+        if constexpr (k == 1) fa[0] = read(vn, 0);
+        else if constexpr (k < 9) fb[1 - s][k == 0 ? 0 : k - 1] = read(vb, k == 0 ? 0 : k - 1);
+        else fa[k - 8] = read(vn, k - 8);
+      }
+      if constexpr (i >= 64 && i % 4 == 0 && i < 64 + 4 * kLoadsA) load_a(pA, cur, Const<(i - 64) / 4>{});
+      if constexpr (i == 90) pA += kt + 5 < nk ? inc_a : 0;
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    repeat<kBlocksM * kBlocksN>(mfma);
+    prv = cur;
+    cur = nxt;
+    nxt = nxt == (kStages - 1) * kLdsStage ? 0 : nxt + kLdsStage;
+    va = vn;
   };
   static_assert(kStages == 4 && kBlocksM == 12 && kBlocksN == 8 && kLoadsA == 6 && kLoadsB == 4,
-                "the group schedule is written for this tile");
+                "the slot schedule is written for this tile");
 
   // Prologue: steps 0..2 and the A part of step 3 in flight (its B part goes
-  // out in groups 0..3 of step 0); wait for step 0; its A blocks 0..5 and B
-  // blocks into registers (A blocks 6..11 are read in groups 0..5).  With
-  // nk == 0 (a device-side K bound of 0) the loads and reads still happen, at
-  // K offset 0, but no MFMA consumes them and the accumulators stay zero.
+  // out in step 0); wait for step 0; its A blocks 0..5 and B blocks into
+  // registers (A blocks 6..11 are read in step 0).  With nk == 0 (a device-side
+  // K bound of 0) the loads and reads still happen, at K offset 0, but no MFMA
+  // consumes them and the accumulators stay zero.
 #pragma unroll
-  for (int st = 0; st < kStages - 1; ++st)
-#pragma unroll
-    for (int q = 0; q < kLoadsA + kLoadsB; ++q) issue_load(st, st, q);
-#pragma unroll
-  for (int q = 0; q < kLoadsA; ++q) issue_load(kStages - 1, kStages - 1, q);
+  for (int st = 0; st < kStages; ++st) {
+    repeat<kLoadsA>([&](auto q) { load_a(pA, st * kLdsStage, q); });
+    pA += st + 1 < nk ? inc_a : 0;
+    if (st < kStages - 1) {
+      repeat<kLoadsB>([&](auto q) { load_b(pB, st * kLdsStage, q); });
+      pB += st + 1 < nk ? inc_b : 0;
+    }
+  }
   stage_barrier<2 * (kLoadsA + kLoadsB) + kLoadsA>();
 #pragma unroll
-  for (int i = 0; i < kBlocksM / 2; ++i) fa[i] = read_a(0, i);
+  for (int i = 0; i < kBlocksM / 2; ++i) fa[i] = read(rdA, i);
 #pragma unroll
-  for (int j = 0; j < kBlocksN; ++j) fb[0][j] = read_b(0, j);
+  for (int j = 0; j < kBlocksN; ++j) fb[0][j] = read(rdB, j);
 
   int kt = 0;
   for (; kt + 1 < nk; kt += 2) {
