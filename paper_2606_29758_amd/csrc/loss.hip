@@ -583,11 +583,6 @@ __global__ void fill_f32_kernel(float* __restrict__ p, int64_t n, float v) {
     p[i] = v;
 }
 
-__global__ void fill_i32_kernel(int32_t* __restrict__ p, int64_t n, int32_t v) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = v;
-}
-
 constexpr int kFinThreads = 256;
 constexpr int kCompactThreads = 256, kCompactPer = 8, kCompactSpan = kCompactThreads * kCompactPer;
 
@@ -984,197 +979,208 @@ __global__ __launch_bounds__(256) void onehot_dh_kernel(int N, int d, const int3
   }
 }
 
-// The dW side groups the backward columns by target id.  Stable bucketing,
-// every result independent of scheduling:
-//   count:  cnt[v] = #{a : ctgt[a] = v}                    (integer atomics)
-//   scan:   start[v] = sum_{u < v} cnt[u]; cursor = start;   the non-empty ids
-//           in increasing order in rows[0 .. *nrows)        (three launches)
-//   fill:   each column takes a slot of its bucket           (arbitrary order)
-//   rank:   column a goes to start[v] + #{b in bucket v : b < a} of `sorted`,
-//           i.e. the bucket in increasing column order.
-// The rank pass reads a column's whole bucket: O(sum_v cnt[v]^2) reads in all,
-// from a bucket that the waves sharing it read together (a few microseconds
-// for uniform targets; about a millisecond if every column had one target).
-__global__ __launch_bounds__(256) void onehot_count_kernel(int N, const int32_t* __restrict__ n_dev,
-                                                           const int32_t* __restrict__ ctgt,
-                                                           int32_t* __restrict__ cnt) {
-  const int n = min(N, *n_dev);
-  for (int a = blockIdx.x * 256 + threadIdx.x; a < n; a += gridDim.x * 256) atomicAdd(&cnt[ctgt[a]], 1);
-}
+// The dW side sums g_i h_i over the backward columns of each target id, in an
+// order that depends on the data alone: the columns are sorted by (target id,
+// column), and the sorted list is cut into spans of kSpan columns, so that the
+// work is even however the ids are spread.  Real token ids follow a 1/rank law
+// (the commonest is several percent of a batch): with one wave per id, as it
+// was, the commonest id's rows were added one after another by a single wave
+// (14.7 ms of a 255 ms pass at 57,000 backward columns, d = 3584; its in-bucket
+// ranks and contended counters another 0.5 ms).  Sort, merge, spans and
+// fix-up together now take 0.38 ms there.
+//
+// Keys are target id << 32 | column: all different, so the order is unique.
+constexpr int kSortSpan = 8192, kSortThreads = 1024;
 
-// The scan in three launches over blocks of kScanSpan ids (256 threads x 16
-// consecutive ids each): per-block totals of cnt and of non-empty ids; their
-// exclusive scan (one work-group, 256 blocks at a time); then each block's
-// outputs from its offsets and a work-group scan of its threads' totals.
-constexpr int kScanPer = 16, kScanSpan = 256 * kScanPer;
-
-// Exclusive scan of one value per thread over a 256-thread work-group; also
-// returns the work-group total.
-__device__ int block_exclusive_scan(int v, int* sh, int& total) {
-  sh[threadIdx.x] = v;
+// Block b: the keys of columns b * kSortSpan .. in increasing order (a bitonic
+// sort in LDS over the next power of two; the padding keys sort last).
+__global__ __launch_bounds__(kSortThreads) void onehot_sort_kernel(int N, const int32_t* __restrict__ n_dev,
+                                                                   const int32_t* __restrict__ ctgt,
+                                                                   uint64_t* __restrict__ keys) {
+  __shared__ uint64_t sh[kSortSpan];
+  const int n = min(N, *n_dev), base = blockIdx.x * kSortSpan, cnt = min(n - base, kSortSpan);
+  if (cnt <= 0) return;   // uniform over the block
+  int size = 1;
+  while (size < cnt) size <<= 1;
+  for (int i = threadIdx.x; i < size; i += kSortThreads)
+    sh[i] = i < cnt ? (uint64_t)(uint32_t)ctgt[base + i] << 32 | (uint32_t)(base + i) : ~0ull;
   __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {
-    const int a = threadIdx.x >= off ? sh[threadIdx.x - off] : 0;
-    __syncthreads();
-    sh[threadIdx.x] += a;
-    __syncthreads();
-  }
-  total = sh[255];
-  const int r = sh[threadIdx.x] - v;
-  __syncthreads();
-  return r;
-}
-
-__global__ __launch_bounds__(256) void onehot_scan_totals_kernel(int V, const int32_t* __restrict__ cnt,
-                                                                 int32_t* __restrict__ tot) {
-  __shared__ int sh[256];
-  const int v0 = blockIdx.x * kScanSpan + threadIdx.x * kScanPer;
-  int c = 0, r = 0;
-#pragma unroll
-  for (int e = 0; e < kScanPer; ++e) {
-    const int k = v0 + e < V ? cnt[v0 + e] : 0;
-    c += k;
-    r += k > 0 ? 1 : 0;
-  }
-  int tc, tr;
-  block_exclusive_scan(c, sh, tc);
-  block_exclusive_scan(r, sh, tr);
-  if (threadIdx.x == 0) {
-    tot[2 * blockIdx.x] = tc;
-    tot[2 * blockIdx.x + 1] = tr;
-  }
-}
-
-// One work-group: tot (a pair per block) -> exclusive offsets in place; the
-// number of non-empty ids to *nrows.
-__global__ __launch_bounds__(256) void onehot_scan_offsets_kernel(int nblk, int32_t* __restrict__ tot,
-                                                                  int32_t* __restrict__ nrows) {
-  __shared__ int sh[256];
-  int base_c = 0, base_r = 0;
-  for (int b0 = 0; b0 < nblk; b0 += 256) {
-    const int b = b0 + threadIdx.x;
-    const int c = b < nblk ? tot[2 * b] : 0, r = b < nblk ? tot[2 * b + 1] : 0;
-    int tc, tr;
-    const int ec = block_exclusive_scan(c, sh, tc);
-    const int er = block_exclusive_scan(r, sh, tr);
-    if (b < nblk) {
-      tot[2 * b] = base_c + ec;
-      tot[2 * b + 1] = base_r + er;
-    }
-    base_c += tc;
-    base_r += tr;
-  }
-  if (threadIdx.x == 0) *nrows = base_r;
-}
-
-// start[v] = sum_{u < v} cnt[u]; cursor = start; the non-empty ids in
-// increasing order in rows.
-__global__ __launch_bounds__(256) void onehot_scan_write_kernel(int V, const int32_t* __restrict__ cnt,
-                                                                const int32_t* __restrict__ off,
-                                                                int32_t* __restrict__ start,
-                                                                int32_t* __restrict__ cursor,
-                                                                int32_t* __restrict__ rows) {
-  __shared__ int sh[256];
-  const int v0 = blockIdx.x * kScanSpan + threadIdx.x * kScanPer;
-  int k[kScanPer];
-  int c = 0, r = 0;
-#pragma unroll
-  for (int e = 0; e < kScanPer; ++e) {
-    k[e] = v0 + e < V ? cnt[v0 + e] : 0;
-    c += k[e];
-    r += k[e] > 0 ? 1 : 0;
-  }
-  int tc, tr;
-  c = off[2 * blockIdx.x] + block_exclusive_scan(c, sh, tc);
-  r = off[2 * blockIdx.x + 1] + block_exclusive_scan(r, sh, tr);
-#pragma unroll
-  for (int e = 0; e < kScanPer; ++e) {
-    if (v0 + e < V) {
-      start[v0 + e] = c;
-      cursor[v0 + e] = c;
-      if (k[e] > 0) rows[r++] = v0 + e;
-      c += k[e];
+  for (int k = 2; k <= size; k <<= 1) {
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      for (int q = threadIdx.x; q < size / 2; q += kSortThreads) {
+        const int i = (q & ~(j - 1)) * 2 + (q & (j - 1));   // the lower index of pair q at distance j
+        const uint64_t x = sh[i], y = sh[i + j];
+        if ((x > y) == ((i & k) == 0)) {
+          sh[i] = y;
+          sh[i + j] = x;
+        }
+      }
+      __syncthreads();
     }
   }
+  for (int i = threadIdx.x; i < cnt; i += kSortThreads) keys[base + i] = sh[i];
 }
 
-__global__ __launch_bounds__(256) void onehot_fill_kernel(int N, const int32_t* __restrict__ n_dev,
-                                                          const int32_t* __restrict__ ctgt,
-                                                          int32_t* __restrict__ cursor, int32_t* __restrict__ tmp) {
+// Merges the sorted blocks: a key's place is its place in its own block plus,
+// for every other block, the number of smaller keys there (a binary search;
+// four blocks at a time, whose loads overlap).
+__global__ __launch_bounds__(256) void onehot_merge_kernel(int N, const int32_t* __restrict__ n_dev,
+                                                           const uint64_t* __restrict__ keys,
+                                                           uint64_t* __restrict__ sorted) {
   const int n = min(N, *n_dev);
-  for (int a = blockIdx.x * 256 + threadIdx.x; a < n; a += gridDim.x * 256) tmp[atomicAdd(&cursor[ctgt[a]], 1)] = a;
-}
-
-__global__ __launch_bounds__(256) void onehot_rank_kernel(int N, const int32_t* __restrict__ n_dev,
-                                                          const int32_t* __restrict__ ctgt,
-                                                          const int32_t* __restrict__ start,
-                                                          const int32_t* __restrict__ cnt,
-                                                          const int32_t* __restrict__ tmp,
-                                                          int32_t* __restrict__ sorted) {
-  const int n = min(N, *n_dev);
-  for (int a = blockIdx.x * 256 + threadIdx.x; a < n; a += gridDim.x * 256) {
-    const int v = ctgt[a], s = start[v], e = s + cnt[v];
-    int rank = 0;
-    for (int k = s; k < e; ++k) rank += tmp[k] < a ? 1 : 0;
-    sorted[s + rank] = a;
-  }
-}
-
-// dW[v] += sum over the bucket of v, in increasing column order, of
-// cg1[a] * h[act[a]] (App. D: the target entries of the head scores), the sum
-// accumulated in float32 and then added to the row.  One wave per non-empty
-// id rows[k], k < *nrows (<= the launch's row bound); 8 features per lane and
-// step, kOnehotSteps steps of the row per pass over the bucket.  d % 8 == 0.
-// Grid ceil(bound / 4), 256 threads.
-constexpr int kOnehotSteps = 8;   // 8 x 8 features per lane: 4096 of the row per pass over the bucket
-
-__global__ __launch_bounds__(256) void onehot_dw_kernel(int bound, int d, const int32_t* __restrict__ nrows,
-                                                        const int32_t* __restrict__ rows,
-                                                        const int32_t* __restrict__ start,
-                                                        const int32_t* __restrict__ cnt,
-                                                        const int32_t* __restrict__ sorted,
-                                                        const int32_t* __restrict__ act,
-                                                        const float* __restrict__ cg1,
-                                                        const uint16_t* __restrict__ hidden, float* __restrict__ dW) {
-  const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (k >= min(bound, *nrows)) return;   // uniform over the wave
-  const int v = rows[k], s = start[v], e = s + cnt[v];
-  const int d8 = d / 8;
-  f32x4* out = reinterpret_cast<f32x4*>(dW + (int64_t)v * d);
-  for (int c0 = 0; c0 < d8; c0 += 64 * kOnehotSteps) {
-    f32x4 lo[kOnehotSteps], hi[kOnehotSteps];
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const uint64_t key = keys[i];
+  const int own = i / kSortSpan, nblk = (n + kSortSpan - 1) / kSortSpan;
+  int place = i - own * kSortSpan;
+  for (int b0 = 0; b0 < nblk; b0 += 4) {
+    int lo[4], len[4];   // the answer lies in [lo, lo + len] of its block
 #pragma unroll
-    for (int q = 0; q < kOnehotSteps; ++q) lo[q] = hi[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int b = s; b < e; ++b) {
-      const int a = sorted[b];
-      const float dl = cg1[a];
-      const u32x4* hr = reinterpret_cast<const u32x4*>(hidden + (int64_t)act[a] * d);
+    for (int u = 0; u < 4; ++u) {
+      const int b = b0 + u;
+      lo[u] = b * kSortSpan;
+      len[u] = b < nblk && b != own ? min(n - b * kSortSpan, kSortSpan) : 0;
+    }
+    for (int bit = kSortSpan; bit > 0; bit >>= 1) {
 #pragma unroll
-      for (int q = 0; q < kOnehotSteps; ++q) {
-        const int c = c0 + q * 64 + lane;
-        if (c < d8) {
-          const u32x4 hv = hr[c];
-          lo[q][0] = fmaf(dl, bf16_lo(hv[0]), lo[q][0]);
-          lo[q][1] = fmaf(dl, bf16_hi(hv[0]), lo[q][1]);
-          lo[q][2] = fmaf(dl, bf16_lo(hv[1]), lo[q][2]);
-          lo[q][3] = fmaf(dl, bf16_hi(hv[1]), lo[q][3]);
-          hi[q][0] = fmaf(dl, bf16_lo(hv[2]), hi[q][0]);
-          hi[q][1] = fmaf(dl, bf16_hi(hv[2]), hi[q][1]);
-          hi[q][2] = fmaf(dl, bf16_lo(hv[3]), hi[q][2]);
-          hi[q][3] = fmaf(dl, bf16_hi(hv[3]), hi[q][3]);
+      for (int u = 0; u < 4; ++u) {
+        if (bit <= len[u] && keys[lo[u] + bit - 1] < key) {
+          lo[u] += bit;
+          len[u] -= bit;
         }
       }
     }
 #pragma unroll
-    for (int q = 0; q < kOnehotSteps; ++q) {
-      const int c = c0 + q * 64 + lane;
-      if (c < d8) {
-        out[2 * c] += lo[q];
-        out[2 * c + 1] += hi[q];
+    for (int u = 0; u < 4; ++u) place += lo[u] - (b0 + u) * kSortSpan;
+  }
+  sorted[place] = key;
+}
+
+// One wave per span of kSpan sorted columns and slice of kSpanSlice features
+// (8 per lane): each run of one id inside the span is accumulated in float32,
+// and added to its dW row when the whole run lies in the span.  A run that
+// comes from the span before (whether or not it ends here) leaves its sum in
+// slab row 2 s, one that starts here and goes on in slab row 2 s + 1.
+// Hidden rows, and the dW rows that are added to, are read eight columns ahead of
+// their use.  d % 8 == 0.
+// Grid (ceil(ceil(N / kSpan) / 4), ceil(d / kSpanSlice)), 256 threads.
+constexpr int kSpan = 32, kSpanSlice = 512, kSpanAhead = 8;
+
+__device__ __forceinline__ int key_id(uint64_t key) { return (int)(key >> 32); }
+
+__global__ __launch_bounds__(256) void onehot_spans_kernel(int N, int d, const int32_t* __restrict__ n_dev,
+                                                           const uint64_t* __restrict__ sorted,
+                                                           const int32_t* __restrict__ act,
+                                                           const float* __restrict__ cg1,
+                                                           const uint16_t* __restrict__ hidden,
+                                                           float* __restrict__ dW, float* __restrict__ slab) {
+  const int n = min(N, *n_dev);
+  const int s = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int lo = s * kSpan;
+  if (lo >= n) return;   // uniform over the wave
+  const int cnt = min(n - lo, kSpan);
+  const int c = blockIdx.y * (kSpanSlice / 8) + lane;   // this lane's 8 features
+  const bool on = c < d / 8;
+  int id = -1, row = 0;
+  float g = 0.f;
+  if (lane < cnt) {
+    const uint64_t key = sorted[lo + lane];
+    const int a = (int)(uint32_t)key;
+    id = key_id(key);
+    row = act[a];
+    g = cg1[a];
+  }
+  const int before = lo > 0 ? key_id(sorted[lo - 1]) : -1;
+  const int after = lo + cnt < n ? key_id(sorted[lo + cnt]) : -1;
+  f32x4 sl = {0.f, 0.f, 0.f, 0.f}, sh = {0.f, 0.f, 0.f, 0.f};
+  for (int b0 = 0; b0 < cnt; b0 += kSpanAhead) {
+    u32x4 hv[kSpanAhead];
+    f32x4 ol[kSpanAhead], oh[kSpanAhead];   // the dW rows of the runs that end here
+#pragma unroll
+    for (int q = 0; q < kSpanAhead; ++q) {
+      const int b = min(b0 + q, cnt - 1);
+      const int r = __builtin_amdgcn_readlane(row, b), v = __builtin_amdgcn_readlane(id, b);
+      const int next = b + 1 < cnt ? __builtin_amdgcn_readlane(id, b + 1) : after;
+      hv[q] = u32x4{0u, 0u, 0u, 0u};
+      ol[q] = oh[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (on) hv[q] = reinterpret_cast<const u32x4*>(hidden + (int64_t)r * d)[c];
+      if (on && next != v && before != v) {
+        const f32x4* o = reinterpret_cast<const f32x4*>(dW + (int64_t)v * d) + 2 * c;
+        ol[q] = o[0];
+        oh[q] = o[1];
       }
     }
+#pragma unroll
+    for (int q = 0; q < kSpanAhead; ++q) {
+      const int b = b0 + q;
+      if (b >= cnt) break;
+      const float gb = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(g), b));
+      sl[0] = fmaf(gb, bf16_lo(hv[q][0]), sl[0]);
+      sl[1] = fmaf(gb, bf16_hi(hv[q][0]), sl[1]);
+      sl[2] = fmaf(gb, bf16_lo(hv[q][1]), sl[2]);
+      sl[3] = fmaf(gb, bf16_hi(hv[q][1]), sl[3]);
+      sh[0] = fmaf(gb, bf16_lo(hv[q][2]), sh[0]);
+      sh[1] = fmaf(gb, bf16_hi(hv[q][2]), sh[1]);
+      sh[2] = fmaf(gb, bf16_lo(hv[q][3]), sh[2]);
+      sh[3] = fmaf(gb, bf16_hi(hv[q][3]), sh[3]);
+      const int v = __builtin_amdgcn_readlane(id, b);
+      const int next = b + 1 < cnt ? __builtin_amdgcn_readlane(id, b + 1) : -1;
+      if (next == v) continue;
+      // the run of v ends at b, or the span does; ids are sorted, so v == before
+      // only in the span's first run
+      const bool came = before == v, goes = b + 1 == cnt && after == v;
+      if (on) {
+        if (came || goes) {
+          f32x4* o = reinterpret_cast<f32x4*>(slab + (int64_t)(2 * s + (came ? 0 : 1)) * d) + 2 * c;
+          o[0] = sl;
+          o[1] = sh;
+        } else {
+          f32x4* o = reinterpret_cast<f32x4*>(dW + (int64_t)v * d) + 2 * c;
+          o[0] = ol[q] + sl;
+          o[1] = oh[q] + sh;
+        }
+      }
+      sl = sh = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
   }
+}
+
+// The runs that cross span ends: the wave of the span a run starts in adds up
+// the run's slab rows in order and adds the sum to the id's dW row.  4 features
+// per lane.  Grid (ceil(ceil(N / kSpan) / 4), ceil(d / 256)), 256 threads.
+__global__ __launch_bounds__(256) void onehot_fixup_kernel(int N, int d, const int32_t* __restrict__ n_dev,
+                                                           const uint64_t* __restrict__ sorted,
+                                                           const float* __restrict__ slab, float* __restrict__ dW) {
+  const int n = min(N, *n_dev);
+  const int s = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int lo = s * kSpan, end = lo + kSpan;
+  if (end >= n) return;   // uniform over the wave; the last span's runs go nowhere
+  const int v = key_id(sorted[end - 1]);
+  if (key_id(sorted[end]) != v) return;                                                // nothing goes on
+  if (lo > 0 && key_id(sorted[lo]) == v && key_id(sorted[lo - 1]) == v) return;        // it started earlier
+  int a = end, b = n;   // first sorted position past the run of v
+  while (a < b) {
+    const int m = (a + b) >> 1;
+    if (key_id(sorted[m]) <= v) a = m + 1;
+    else b = m;
+  }
+  const int last = (a - 1) / kSpan;
+  const int c = blockIdx.y * 64 + lane;
+  if (c >= d / 4) return;
+  const f32x4* part = reinterpret_cast<const f32x4*>(slab) + c;
+  const int64_t ld = d / 4;
+  f32x4 sum = part[(2 * (int64_t)s + 1) * ld];
+  int q = s + 1;
+  for (; q + 7 <= last; q += 8) {
+    f32x4 x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = part[2 * (int64_t)(q + e) * ld];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sum += x[e];
+  }
+  for (; q <= last; ++q) sum += part[2 * (int64_t)q * ld];
+  f32x4* o = reinterpret_cast<f32x4*>(dW + (int64_t)v * d) + c;
+  *o += sum;
 }
 
 // ---------------------------------------------------------------------------
@@ -1187,8 +1193,7 @@ struct Plan {
   int64_t Dk;   // K of the products over the hidden features: d rounded up to 32 (zero padding)
   int64_t off_pm, off_pl, off_zt, off_lse, off_delta, off_fidx, off_fpos, off_nfwd, off_idx, off_nact, off_afwd,
       off_ctgt, off_clse, off_cdelta, off_cg1, off_ftgt, off_cnt, off_blk, off_wk, off_hk, off_ht, off_wt, off_dn, off_dt,
-      off_slab, off_zk, off_oh_cnt, off_oh_start, off_oh_cursor, off_oh_rows, off_oh_nrows, off_oh_tot, off_oh_tmp,
-      off_oh_sorted, total;
+      off_slab, off_zk, off_oh_keys, off_oh_sorted, total;
   bool keep;   // the forward keeps the first chunk's logits (fp16 offsets from the tile maxima)
 };
 
@@ -1251,19 +1256,15 @@ Plan make_plan(int64_t N, int64_t d, int64_t V, bool keep) {
   p.off_hk = take(d64 * p.Npad * 2);                                  // gathered hidden rows [d64/32][Npad][32]
   p.off_ht = take(p.dpad * p.Npad * 2);                               // H[bwd]^T [Npad/32][dpad][32]
   p.off_wt = take(p.dpad * ((p.Vpad + p.Vc - 1) / p.Vc) * p.Vc * 2);  // per chunk: W^T [Vc/32][dpad][32]
-  p.off_dn = take(p.Npad * p.Vc * 2);                                 // [Npad/768][Vc/32][768][32] (token blocks)
+  // [Npad/768][Vc/32][768][32] (token blocks); after the products, the partial
+  // sums of the target-entry spans (two rows of d floats per span)
+  p.off_dn = take(std::max(p.Npad * p.Vc * 2, (p.Npad / kSpan) * 2 * d * 4));
   p.off_dt = take(p.Vc * p.Npad * 2);                                 // [Vc/384][Npad/32][384][32] (vocabulary blocks)
   p.off_slab = take((int64_t)kNumXcd * kTailSlots * kTileM * kTileN * 4);   // K parts of tail tiles
   p.keep = keep;
   p.off_zk = take(keep ? p.Vc * p.Npad * 2 : 0);                      // kept fp16 logit offsets, one block per forward tile
-  p.off_oh_cnt = take(V * 4);                                         // one-hot part: backward columns per target id,
-  p.off_oh_start = take(V * 4);                                       //   bucket starts, fill cursors,
-  p.off_oh_cursor = take(V * 4);
-  p.off_oh_rows = take(V * 4);                                        //   non-empty ids and their count,
-  p.off_oh_nrows = take(4);
-  p.off_oh_tot = take((V + kScanSpan - 1) / kScanSpan * 8);           //   per-block totals of the scan
-  p.off_oh_tmp = take(p.Npad * 4);                                    //   buckets unordered, then in column order
-  p.off_oh_sorted = take(p.Npad * 4);
+  p.off_oh_keys = take(p.Npad * 8);                                   // target-entry keys of the backward columns:
+  p.off_oh_sorted = take(p.Npad * 8);                                 //   sorted per block, sorted
   p.total = o;
   return p;
 }
@@ -1384,14 +1385,8 @@ int pspo_loss_fwd_bwd(const uint16_t* hidden, const uint16_t* w_head, const int3
   uint16_t* dT = reinterpret_cast<uint16_t*>(ws + pl.off_dt);
   uint16_t* zk = pl.keep ? reinterpret_cast<uint16_t*>(ws + pl.off_zk) : nullptr;
   float* slab = reinterpret_cast<float*>(ws + pl.off_slab);
-  int32_t* oh_cnt = reinterpret_cast<int32_t*>(ws + pl.off_oh_cnt);
-  int32_t* oh_start = reinterpret_cast<int32_t*>(ws + pl.off_oh_start);
-  int32_t* oh_cursor = reinterpret_cast<int32_t*>(ws + pl.off_oh_cursor);
-  int32_t* oh_rows = reinterpret_cast<int32_t*>(ws + pl.off_oh_rows);
-  int32_t* oh_nrows = reinterpret_cast<int32_t*>(ws + pl.off_oh_nrows);
-  int32_t* oh_tot = reinterpret_cast<int32_t*>(ws + pl.off_oh_tot);
-  int32_t* oh_tmp = reinterpret_cast<int32_t*>(ws + pl.off_oh_tmp);
-  int32_t* oh_sorted = reinterpret_cast<int32_t*>(ws + pl.off_oh_sorted);
+  uint64_t* oh_keys = reinterpret_cast<uint64_t*>(ws + pl.off_oh_keys);
+  uint64_t* oh_sorted = reinterpret_cast<uint64_t*>(ws + pl.off_oh_sorted);
   const int Dk = (int)pl.Dk;
 
   const int tiles_tok_n = (int)(pl.Npad / kTileN);    // tokens on the B side
@@ -1515,32 +1510,28 @@ int pspo_loss_fwd_bwd(const uint16_t* hidden, const uint16_t* w_head, const int3
     }
   }
   // 7. the target entries of the logit gradient, in float32: the backward
-  //    columns bucketed by target id in column order, then dW[v] += the sum
-  //    of each bucket's g h rows and d_hidden += g W[o] row by row
+  //    columns sorted by target id and column, then dW[v] += the sum of each
+  //    id's g h rows and d_hidden += g W[o] row by row
   {
-    const unsigned gcols = (unsigned)std::min<int64_t>((pl.Npad + 255) / 256, 1024);
-    hipLaunchKernelGGL(fill_i32_kernel, dim3((unsigned)std::min<int64_t>((V + 255) / 256, 1024)), dim3(256), 0,
-                       stream, oh_cnt, (int64_t)V, 0);
-    PSPO_LAUNCHED("fill_i32_kernel", stream);
-    hipLaunchKernelGGL(onehot_count_kernel, dim3(gcols), dim3(256), 0, stream, N, n_act, act_tgt, oh_cnt);
-    PSPO_LAUNCHED("onehot_count_kernel", stream);
-    const unsigned nscan = (unsigned)((V + kScanSpan - 1) / kScanSpan);
-    hipLaunchKernelGGL(onehot_scan_totals_kernel, dim3(nscan), dim3(256), 0, stream, V, oh_cnt, oh_tot);
-    PSPO_LAUNCHED("onehot_scan_totals_kernel", stream);
-    hipLaunchKernelGGL(onehot_scan_offsets_kernel, dim3(1), dim3(256), 0, stream, (int)nscan, oh_tot, oh_nrows);
-    PSPO_LAUNCHED("onehot_scan_offsets_kernel", stream);
-    hipLaunchKernelGGL(onehot_scan_write_kernel, dim3(nscan), dim3(256), 0, stream, V, oh_cnt, oh_tot, oh_start,
-                       oh_cursor, oh_rows);
-    PSPO_LAUNCHED("onehot_scan_write_kernel", stream);
-    hipLaunchKernelGGL(onehot_fill_kernel, dim3(gcols), dim3(256), 0, stream, N, n_act, act_tgt, oh_cursor, oh_tmp);
-    PSPO_LAUNCHED("onehot_fill_kernel", stream);
-    hipLaunchKernelGGL(onehot_rank_kernel, dim3(gcols), dim3(256), 0, stream, N, n_act, act_tgt, oh_start, oh_cnt,
-                       oh_tmp, oh_sorted);
-    PSPO_LAUNCHED("onehot_rank_kernel", stream);
-    const int rows_bound = std::min(N, V);
-    hipLaunchKernelGGL(onehot_dw_kernel, dim3((unsigned)((rows_bound + 3) / 4)), dim3(256), 0, stream, rows_bound, d,
-                       oh_nrows, oh_rows, oh_start, oh_cnt, oh_sorted, act_idx, act_g1, hidden, d_w_head);
-    PSPO_LAUNCHED("onehot_dw_kernel", stream);
+    const unsigned nsort = (unsigned)((N + kSortSpan - 1) / kSortSpan);
+    hipLaunchKernelGGL(onehot_sort_kernel, dim3(nsort), dim3(kSortThreads), 0, stream, N, n_act, act_tgt, oh_keys);
+    PSPO_LAUNCHED("onehot_sort_kernel", stream);
+    if (nsort > 1) {   // (one block's keys are sorted already)
+      hipLaunchKernelGGL(onehot_merge_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, stream, N, n_act, oh_keys,
+                         oh_sorted);
+      PSPO_LAUNCHED("onehot_merge_kernel", stream);
+    }
+    const uint64_t* order = nsort > 1 ? oh_sorted : oh_keys;
+    float* oh_slab = reinterpret_cast<float*>(dN);
+    const unsigned gspan = (unsigned)(((N + kSpan - 1) / kSpan + 3) / 4);
+    hipLaunchKernelGGL(onehot_spans_kernel, dim3(gspan, (unsigned)((d + kSpanSlice - 1) / kSpanSlice)), dim3(256), 0,
+                       stream, N, d, n_act, order, act_idx, act_g1, hidden, d_w_head, oh_slab);
+    PSPO_LAUNCHED("onehot_spans_kernel", stream);
+    if (N > kSpan) {   // (one span: no run crosses its end)
+      hipLaunchKernelGGL(onehot_fixup_kernel, dim3(gspan, (unsigned)((d + 255) / 256)), dim3(256), 0, stream, N, d, n_act,
+                         order, oh_slab, d_w_head);
+      PSPO_LAUNCHED("onehot_fixup_kernel", stream);
+    }
     hipLaunchKernelGGL(onehot_dh_kernel, dim3((unsigned)((N + 3) / 4)), dim3(256), 0, stream, N, d, n_act, act_idx,
                        act_tgt, act_g1, w_head, d_hidden);
     PSPO_LAUNCHED("onehot_dh_kernel", stream);

@@ -1,0 +1,72 @@
+"""GPU: the float32 target entries of dW, against the float64 oracle, where their summation can go
+wrong: column counts around a span (32) and a sorted block (8192), ids whose columns fill many spans
+(one id for every token; a 1/rank law, as real token ids follow), end on a span's edge or hold one
+column each, and widths around a wave's 256- and 512-feature slices.
+
+Tolerance of row v: the target entries are exact to float32 (1e-5 of the row); every other entry
+-delta_i p_iv is rounded to bf16, at most 2^-9 of it, in directions h_i that are independent, so the
+row is off by about 2^-9 sqrt(sum_i (delta_i p_iv |h_i|)^2) at most; twice that is allowed.  Losing or
+doubling one column of the largest bucket (16,500) of random hidden rows moves its row by more than
+ten times as much.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ppo_head as ohead
+from paper_2606_29758_amd import pspo, synth
+
+from parity_util import f32
+
+pytestmark = pytest.mark.gpu
+
+CASES = [(1, 24, "one"), (31, 24, "one"), (32, 24, "one"), (33, 24, "one"), (64, 8, "pairs"), (65, 1032, "ranked"),
+         (97, 24, "distinct"), (640, 264, "spans"), (2050, 520, "ranked"), (8191, 24, "one"), (8192, 24, "ranked"),
+         (8193, 24, "ranked"), (16500, 24, "one"), (16500, 256, "ranked")]
+
+
+def _targets(rng, N, V, law):
+    if law == "one":
+        return np.full(N, V - 1)
+    if law == "pairs":
+        return np.arange(N) // 2 % V
+    if law == "distinct":
+        return rng.permutation(V)[np.arange(N) % V]
+    if law == "spans":      # each id holds exactly two spans of the sorted columns
+        return rng.permutation(np.arange(N) // 64)
+    return np.minimum((V + 1.0) ** rng.random(N), V).astype(np.int64) - 1
+
+
+@pytest.mark.parametrize("N,d,law", CASES)
+def test_target_rows(N, d, law):
+    print(f"[target entries] N={N} d={d} law={law}", flush=True)
+    V, R = 97, 4
+    rng = np.random.default_rng(N + d)
+    h = synth.round_to_bf16_bits(rng.normal(0.0, 1.0, (N, d)).astype(np.float32))
+    W = synth.round_to_bf16_bits(rng.normal(0.0, 0.1 / np.sqrt(d), (V, d)).astype(np.float32))
+    tgt = _targets(rng, N, V, law).astype(np.int32)
+    seq = np.sort(rng.integers(0, R, N)).astype(np.int32)
+    adv = np.array([1.0, -1.0, 0.0, 0.5], dtype=np.float32)
+    weight = (1.0 + rng.random(N)).astype(np.float32)
+    lp_old = (ohead.target_logprob(h, W, tgt) + rng.normal(0.0, 0.05, N)).astype(np.float32)
+    ref = ohead.loss_fwd_bwd(h, W, tgt, lp_old, weight, seq, adv, f32(0.9), f32(0.9), f32(0.25))
+    t = lambda a, dt: torch.from_numpy(np.ascontiguousarray(a)).to(device="cuda", dtype=dt)   # noqa: E731
+    bits = lambda b: torch.from_numpy(b.view(np.int16)).to("cuda").view(torch.bfloat16)       # noqa: E731
+    args = (bits(h), bits(W), t(tgt, torch.int32), t(lp_old, torch.float32), t(weight, torch.float32),
+            t(seq, torch.int32), t(adv, torch.float32), N, 0.9, 0.9, 0.25)
+    out = pspo.loss_fwd_bwd(*args)
+    dw = out["d_w_head"].clone()
+    torch.cuda.synchronize()
+    got, want = dw.double().cpu().numpy(), ref["d_w"]
+    f = lambda b: (b.astype(np.uint32) << 16).view(np.float32).astype(np.float64)             # noqa: E731
+    z = f(h) @ f(W).T
+    p = np.exp(z - z.max(axis=1, keepdims=True))
+    p /= p.sum(axis=1, keepdims=True)
+    p[np.arange(N), tgt] = 0.0
+    rounding = np.sqrt(((ref["delta"][:, None] * p) ** 2 * (f(h) ** 2).sum(axis=1)[:, None]).sum(axis=0))
+    bound = 2.0 ** -8 * rounding + 1e-5 * np.linalg.norm(want, axis=1)
+    off = np.linalg.norm(got - want, axis=1)
+    v = int(np.argmax(off / np.maximum(bound, 1e-300)))
+    assert np.all(off <= bound), (v, off[v], bound[v], int((tgt == v).sum()))
+    again = pspo.loss_fwd_bwd(*args)["d_w_head"]
+    assert torch.equal(again, dw)      # the order of every sum is fixed
