@@ -43,6 +43,7 @@
 #include "common.h"
 #include "gemm.h"
 #include "layout.h"
+#include "partials.h"
 #include "rowdot.h"
 
 namespace pspo {
@@ -727,43 +728,45 @@ __device__ T block_sum(T v, T* sh) {
   return r;
 }
 
-__device__ float block_max(float v, float* sh) {
-  sh[threadIdx.x] = v;
-  __syncthreads();
-  for (int s = kFinThreads / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) sh[threadIdx.x] = fmaxf(sh[threadIdx.x], sh[threadIdx.x + s]);
-    __syncthreads();
-  }
-  float r = sh[0];
-  __syncthreads();
-  return r;
+// Sum and maximum over the 32 lanes of a half wave.
+__device__ __forceinline__ double half_sum(double v) {
+#pragma unroll
+  for (int o = kMergeCols / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
+__device__ __forceinline__ float half_max(float v) {
+#pragma unroll
+  for (int o = kMergeCols / 2; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+  return v;
 }
 
 // Per token: merge the vocabulary-tile partials into lse, then the PPO terms.
-// Each block writes (sum c s, sum |c s|, #clipped, #A==0) and max c to blk[5*b].
-__global__ __launch_bounds__(kFinThreads) void finalize_kernel(
+// Each block (kMergeCols tokens) writes (sum c s, sum |c s|, #clipped, #A==0)
+// and max c to blk[5*b].
+__global__ __launch_bounds__(kMergeThreads) void finalize_kernel(
     int N, int V, int R, int ntv, int64_t ldp, const float* __restrict__ part_m, const float* __restrict__ part_l,
     const float* __restrict__ zt, const int32_t* __restrict__ fwd_pos, const int32_t* __restrict__ target,
     const float* __restrict__ logp_old,
     const float* __restrict__ weight, const int32_t* __restrict__ seq_id, const float* __restrict__ adv,
     float eps_low, float eps_high, float loss_scale, float* __restrict__ lse_out, float* __restrict__ delta_out,
     float* __restrict__ logp_new, double* __restrict__ blk, int32_t* __restrict__ err_flag) {
-  __shared__ double shd[kFinThreads];
-  __shared__ float shf[kFinThreads];
-  const int t = blockIdx.x * kFinThreads + threadIdx.x;
+  __shared__ MergeRow sh[kMergeSlices];
+  const int t = blockIdx.x * kMergeCols + threadIdx.x % kMergeCols;
+  // column of this token's forward partials; -1: its logits were not needed
+  const int col = t < N ? fwd_pos[t] : -1;
+  const float M = merge_max(part_m, ntv, ldp, col, sh);
+  float part = 0.f;
+  if (col >= 0) {
+#pragma unroll 4
+    for (int k = threadIdx.x / kMergeCols; k < ntv; k += kMergeSlices)
+      part += part_l[k * ldp + col] * __expf(part_m[k * ldp + col] - M);
+  }
+  const float L = merge_sum(part, sh);
+  if (threadIdx.x >= kMergeCols) return;
   double cs = 0.0, acs = 0.0, nclip = 0.0, nzero = 0.0;
   float maxw = 0.f;
   if (t < N) {
-    // column of this token's forward partials; -1: its logits were not needed
-    const int col = fwd_pos[t];
-    float lse = NAN;
-    if (col >= 0) {
-      float M = kNegInf;
-      for (int k = 0; k < ntv; ++k) M = fmaxf(M, part_m[k * ldp + col]);
-      float L = 0.f;
-      for (int k = 0; k < ntv; ++k) L += part_l[k * ldp + col] * __expf(part_m[k * ldp + col] - M);
-      lse = M + logf(L);
-    }
+    const float lse = col >= 0 ? M + logf(L) : NAN;
     const int tgt = target[t];
     const int seq = seq_id[t];
     const bool valid = tgt >= 0 && tgt < V && seq >= 0 && seq < R;
@@ -795,11 +798,11 @@ __global__ __launch_bounds__(kFinThreads) void finalize_kernel(
     nzero = (A == 0.f) ? 1.0 : 0.0;
     maxw = c;
   }
-  cs = block_sum(cs, shd);
-  acs = block_sum(acs, shd);
-  nclip = block_sum(nclip, shd);
-  nzero = block_sum(nzero, shd);
-  maxw = block_max(maxw, shf);
+  cs = half_sum(cs);
+  acs = half_sum(acs);
+  nclip = half_sum(nclip);
+  nzero = half_sum(nzero);
+  maxw = half_max(maxw);
   if (threadIdx.x == 0) {
     double* o = blk + 5 * (int64_t)blockIdx.x;
     o[0] = cs;
@@ -817,6 +820,7 @@ __global__ __launch_bounds__(kFinThreads) void reduce_loss_kernel(int nblk, cons
   __shared__ double shd[kFinThreads];
   double v[4] = {0, 0, 0, 0};
   double mx = 0.0;
+#pragma unroll 4
   for (int b = threadIdx.x; b < nblk; b += kFinThreads) {
     for (int k = 0; k < 4; ++k) v[k] += blk[5 * (int64_t)b + k];
     mx = fmax(mx, blk[5 * (int64_t)b + 4]);
@@ -1227,7 +1231,7 @@ Plan make_plan(int64_t N, int64_t d, int64_t V, bool keep) {
     p.Vc = round_up((p.Vpad + nch - 1) / nch, kTileM);
   }
   p.ntv = p.Vpad / kTileM;
-  p.nfin = (N + kFinThreads - 1) / kFinThreads;
+  p.nfin = (N + kMergeCols - 1) / kMergeCols;
   int64_t o = 0;
   auto take = [&](int64_t bytes) {
     const int64_t at = o;
@@ -1434,7 +1438,7 @@ int pspo_loss_fwd_bwd(const uint16_t* hidden, const uint16_t* w_head, const int3
                      fwd_idx, fwd_tgt, n_fwd, zt, nullptr);
   PSPO_LAUNCHED("row_dots_kernel", stream);
   // 3. lse, PPO terms, delta, loss
-  hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)pl.nfin), dim3(kFinThreads), 0, stream, N, V, R, tiles_voc,
+  hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)pl.nfin), dim3(kMergeThreads), 0, stream, N, V, R, tiles_voc,
                      pl.Npad, part_m, part_l, zt, fwd_pos, target, logp_old, weight, seq_id, advantage, eps_low,
                      eps_high, loss_scale, lse, delta, logp_new, blk, err_flag);
   PSPO_LAUNCHED("finalize_kernel", stream);

@@ -1,0 +1,57 @@
+// Merging the per-vocabulary-tile softmax partials of the logit products.
+//
+// A product leaves, for every column (token) and vocabulary tile k < ntv, the
+// tile's maximum at part_m[k * ldp + col] and its sums relative to it.  They
+// are merged by blocks of kMergeThreads threads that take kMergeCols columns
+// with kMergeSlices threads each; slice s takes the tiles s, s + kMergeSlices,
+// ... in order and the slices are joined in a fixed tree, so the result depends
+// on the partials alone.  What bounds a merge is the latency of its loads: one
+// thread per column walked the 396 tiles of V = 152064 twice, with 1 block in
+// flight per 256 tokens (294 us for 2,048 tokens, 306 us for 200, 402 us for
+// the proxy of 1,501); with 32 slices it takes MERGE_US.
+#pragma once
+
+#include "common.h"
+
+namespace pspo {
+namespace {
+
+constexpr int kMergeCols = 32, kMergeSlices = 32, kMergeThreads = kMergeCols * kMergeSlices;
+
+// LDS of a merge: one value per (slice, column).
+typedef float MergeRow[kMergeCols];
+
+// op over the kMergeSlices values of the thread's column, in a fixed tree;
+// every thread of the block calls it and gets its column's result.
+template <class Op>
+__device__ __forceinline__ float merge_slices(float x, MergeRow* sh, Op op) {
+  const int c = threadIdx.x % kMergeCols, s = threadIdx.x / kMergeCols;
+  sh[s][c] = x;
+  __syncthreads();
+#pragma unroll
+  for (int h = kMergeSlices / 2; h > 0; h >>= 1) {
+    if (s < h) sh[s][c] = op(sh[s][c], sh[s + h][c]);
+    __syncthreads();
+  }
+  x = sh[0][c];
+  __syncthreads();
+  return x;
+}
+
+// The maximum of column `col` over its tiles (-inf where col < 0).
+__device__ __forceinline__ float merge_max(const float* __restrict__ part_m, int ntv, int64_t ldp, int col,
+                                           MergeRow* sh) {
+  float m = -INFINITY;
+  if (col >= 0) {
+#pragma unroll 8
+    for (int k = threadIdx.x / kMergeCols; k < ntv; k += kMergeSlices) m = fmaxf(m, part_m[k * ldp + col]);
+  }
+  return merge_slices(m, sh, [](float a, float b) { return fmaxf(a, b); });
+}
+
+__device__ __forceinline__ float merge_sum(float x, MergeRow* sh) {
+  return merge_slices(x, sh, [](float a, float b) { return a + b; });
+}
+
+}  // namespace
+}  // namespace pspo
