@@ -21,9 +21,7 @@
 // (H uniform on 1..T) and Time prior (xi_t = exp(-lambda (t-1))).  Every xi is
 // floored at 2^-32, the resolution of the sampler's thresholds.
 //
-// Both kernels work in float64; their cost is small next to the proxy's
-// forward pass (a few operations per completion token and per step; the
-// design's sequential solve reads LDS-resident weights and block stack).
+// Both kernels work in float64.
 #include <cmath>
 #include <mutex>
 #include <string>
@@ -128,171 +126,359 @@ __global__ __launch_bounds__(256) void design_weights_kernel(
   }
 }
 
-// The budgeted monotone solve of one prompt (App. F) on the storage given: wr
-// the weights, wv / ln the block stack (summed weight and length of each
-// block), rest the suffix sums (it may alias wr: the weights are not read
-// after the pooling).  Force-inlined at each call with pointers of one memory
-// kind, so that LDS-resident data is read and written by LDS instructions
-// rather than generic ones.  Called by all 64 lanes of the block's one wave:
-// lane 0 pools, the lanes compute the block scores, lane 0 does the rest.
-__device__ __forceinline__ void pav_solve(const double* wr, double* wv, int32_t* ln, double* rest, int T,
-                                          double budget, double* xp) {
-  const int lane = threadIdx.x;
-  int M = 0;                       // blocks under the top, then all blocks
-  if (lane == 0) {
-    // Pooling Adjacent Violators: a stack of blocks (start, length, summed
-    // weight); a new element pools with the block below it while that block's
-    // score sqrt(W / L) is below its own.  Scores of positive lengths are in the
-    // order of the mean weights, and tw / tl < W / L exactly when tw L < W tl, so
-    // each step compares two products: no division or root per step (a product
-    // rounds to 2^-53 relative, so the decision can differ from the exact one
-    // only for blocks whose means agree to that; pooling or not such a pair
-    // moves the table by the same relative amount).  The top block stays in
-    // registers (the stack holds the blocks under it), so an element that does
-    // not pool costs no stack access.
-    // A block's start is not stored: the block under the top ends where the top
-    // starts.
-    int ts = 0, tl = 1;              // the top block
-    double tw = wr[0];
-    double w_next = T > 1 ? wr[1] : 0.0;   // each step's weight is read one step ahead
-    for (int t = 1; t < T; ++t) {
-      int s0 = t, L = 1;
-      double W = w_next;
-      if (t + 1 < T) w_next = wr[t + 1];
-      bool top = true;
-      while (top && tw * (double)L < W * (double)tl) {   // pool the top into the new block
-        s0 = ts;
-        L += tl;
-        W = tw + W;
-        if (M > 0) {
-          --M;
-          tl = ln[M];
-          tw = wv[M];
-          ts = s0 - tl;
-        } else {
-          top = false;
-        }
-      }
-      if (top) {                     // the old top goes under the new block
-        ln[M] = tl;
-        wv[M] = tw;
-        ++M;
-      }
-      ts = s0;
-      tl = L;
-      tw = W;
+// The budgeted monotone solve (App. F).  One thread per prompt ran Pooling
+// Adjacent Violators over the steps, one dependent chain of LDS accesses and
+// branches per step, and then summed, searched and wrote the table alone:
+// 1,922 us for 8 prompts of 2,500 to 6,900 steps, 293 us with what follows.
+//
+// The blocks are found first, by all threads: blocks of steps are merged pairwise
+// up a tree, where only the blocks at the joint can violate, and pooling adjacent
+// violators in any order ends at the same blocks.  The sums of this phase are
+// rounded in the order of the tree and only find the blocks.  Each found block's
+// sum is then formed again as the sequential algorithm forms it: run from a block's
+// first step, it pools exactly as it does in a run over all steps (a block's
+// first step never pools with what is before it).  The blocks are independent, so
+// a wave each; the longest block bounds the solve.
+constexpr int kDesignThreads = 1024;
+
+// Storage of one prompt's blocks, all of one memory kind (LDS or the workspace).
+// ln[t] > 0: a block of ln[t] steps starts at t, its summed weight (later its
+// score) at wv[t]; the last step e of a block of L >= 2 steps holds ln[e] = -L,
+// so that the block can be found from its end; ln is 0 or stale but not
+// positive at every other step.  heads: bit t % 64 of word t / 64.
+struct Blocks {
+  double* wv;
+  int32_t* ln;
+  uint64_t* heads;
+};
+
+// Joins the blocks of [a, m) and [m, b): pools the two blocks at m while the left
+// one's mean is below the right one's, then on to both sides.  Scores
+// sqrt(W / L) are in the order of the means, and W1 / L1 < W2 / L2 exactly when
+// W1 L2 < W2 L1: two products and no division (a product rounds to 2^-53
+// relative, so the decision can differ from the exact one only for blocks whose
+// means agree to that; pooling or not such a pair moves the table by the same
+// relative amount).
+__device__ __forceinline__ void join_blocks(const Blocks& bl, int a, int m, int b) {
+  int l = abs(bl.ln[m - 1]), r = bl.ln[m];
+  int s = m - l, e = m;            // the pooled block is [s, e) once a pair has been pooled
+  double W = bl.wv[s], V = bl.wv[m];
+  if (!(W * (double)r < V * (double)l)) return;
+  bool pool_right = true;
+  for (;;) {
+    if (pool_right) {              // [s, e) and the block of r steps at e
+      bl.ln[e] = 0;
+      W += V;
+      l += r;
+      e += r;
     }
-    ln[M] = tl;
-    wv[M] = tw;
-    ++M;
-  }
-  M = __shfl(M, 0);
-  __syncthreads();   // lane 0's stack is visible to every lane
-  // the block scores sqrt(W_m / L_m), spread over the lanes
-  for (int m = lane; m < M; m += 64) wv[m] = sqrt(wv[m] / (double)ln[m]);
-  __syncthreads();
-  if (lane != 0) return;
-  // suffix sums of L_m s_m (accumulated from the last block)
-  // first unsaturated block: kappa(m) = (B - sum_{j<m} L_j) / sum_{j>=m} L_j s_j, kappa(m) s_m <= 1
-  double acc = 0.0;
-  for (int m = M - 1; m >= 0; --m) {
-    acc += (double)ln[m] * wv[m];
-    rest[m] = acc;
-  }
-  int saturated = 0;
-  double kappa = -1.0;   // < 0: only zero-weight blocks remain unsaturated
-  for (int m = 0; m < M; ++m) {
-    if (rest[m] == 0.0) {
-      kappa = -1.0;
-      break;
+    pool_right = false;
+    if (e < b) {
+      r = bl.ln[e];
+      V = bl.wv[e];
+      pool_right = W * (double)r < V * (double)l;
     }
-    kappa = (budget - (double)saturated) / rest[m];
-    if (kappa * wv[m] <= 1.0) break;
-    saturated += ln[m];
+    if (pool_right) continue;
+    if (s == a) break;
+    const int tl = abs(bl.ln[s - 1]);
+    const double tw = bl.wv[s - tl];
+    if (!(tw * (double)l < W * (double)tl)) break;
+    bl.ln[s] = 0;
+    s -= tl;
+    l += tl;
+    W += tw;
   }
-  for (int m = 0, start = 0; m < M; start += ln[m], ++m) {
-    double v;
-    if (kappa < 0.0) v = (start < saturated) ? 1.0 : (budget - (double)saturated) / (double)(T - saturated);
-    else v = fmin(1.0, kappa * wv[m]);
-    v = fmax(v, kXiFloor);
-    for (int t = start; t < start + ln[m]; ++t) xp[t] = v;
+  bl.ln[s] = l;
+  bl.ln[e - 1] = -l;
+  bl.wv[s] = W;
+}
+
+// Bits of the first step of every block of at least `least` steps, over [0, n).
+__device__ __forceinline__ void mark_heads(const Blocks& bl, int n, int least) {
+  for (int t = threadIdx.x; t < (n + 63) / 64 * 64; t += kDesignThreads) {
+    const uint64_t m = __ballot(t < n && bl.ln[t] >= least);
+    if ((threadIdx.x & 63) == 0) bl.heads[t / 64] = m;
   }
 }
 
-// LDS of one design block: the prompt's weights (8 bytes per step) and, when
-// they fit as well, the PAV block stack (12 bytes per step: summed weight and
-// length).
-constexpr int kDesignLdsBytes = 160 * 1024;
+__device__ __forceinline__ double lane_value(double x, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
 
-// One block of 64 threads (one wave) per prompt: the lanes stage the prompt's
-// weights in LDS, check them and sum their square roots; lane 0 then runs the
-// sequential solve on LDS-resident data (the weights when T <= 20480, the
-// block stack too when T <= 8192; otherwise from the workspace).
-__global__ __launch_bounds__(64) void design_cutoffs_kernel(const double* __restrict__ w,
-                                                            const int64_t* __restrict__ xi_off, double budget,
-                                                            int variant, double lambda, double* __restrict__ xi,
-                                                            int32_t* __restrict__ blen,
-                                                            double* __restrict__ bval, int32_t* __restrict__ err_flag) {
+// The sequential algorithm over the steps [s, s + len), by one wave whose lanes
+// all hold the same values: a stack of blocks (length, summed weight); a new step
+// pools with the block below it while that block's mean is below its own.  The
+// stack's first 64 entries sit in the lanes (entry k in lane k), further ones in
+// the block's own wv / ln; the weights are read 64 at a time, one group ahead.
+// It ends with the one block [s, s + len), or with several where the tree's
+// rounding and this one's differ.
+__device__ __forceinline__ void pool_in_order(const Blocks& bl, const double* wp, int s, int len) {
+  const int lane = threadIdx.x & 63;
+  double* wv = bl.wv + s;
+  int32_t* ln = bl.ln + s;
+  const double* w = wp + s;
+  double sw = 0.0;                 // this lane's stack entry
+  int sl = 0;
+  int depth = 0;                   // entries under the top block
+  double group = lane < len ? w[lane] : 0.0, ahead = 64 + lane < len ? w[64 + lane] : 0.0;
+  double tw = lane_value(group, 0), tl = 1.0;
+  for (int t = 1; t < len; ++t) {
+    if ((t & 63) == 0) {
+      group = ahead;
+      ahead = t + 64 + lane < len ? w[t + 64 + lane] : 0.0;
+    }
+    double W = lane_value(group, t & 63), L = 1.0;
+    bool under = true;             // a block is left under the new one
+    while (under && tw * L < W * tl) {
+      L += tl;
+      W = tw + W;
+      under = depth > 0;
+      if (under) {
+        --depth;
+        if (depth < 64) {
+          tw = lane_value(sw, depth);
+          tl = (double)__builtin_amdgcn_readlane(sl, depth);
+        } else {
+          tw = lane_value(wv[depth], 0);
+          tl = (double)__builtin_amdgcn_readfirstlane(ln[depth]);
+        }
+      }
+    }
+    if (under) {
+      if (depth < 64) {
+        if (lane == depth) {
+          sw = tw;
+          sl = (int)tl;
+        }
+      } else {                     // (every lane writes the same, and so reads what it wrote)
+        wv[depth] = tw;
+        ln[depth] = (int)tl;
+      }
+      ++depth;
+    }
+    tw = W;
+    tl = L;
+  }
+  // from the last block to the first: entry k starts at or after step k, so no
+  // entry is overwritten before it is read
+  for (int k = depth, end = len; k >= 0; --k) {
+    if (k < depth) {
+      tw = k < 64 ? lane_value(sw, k) : wv[k];
+      tl = k < 64 ? (double)__builtin_amdgcn_readlane(sl, k) : (double)ln[k];
+    }
+    const int l = (int)tl, start = end - l;
+    for (int t = start + 1 + lane; t < end; t += 64) ln[t] = 0;
+    if (lane == 0) {
+      ln[start] = l;
+      wv[start] = tw;
+    }
+    end = start;
+  }
+}
+
+// The solve of one prompt of T steps whose last positive weight is step n - 1
+// (trailing steps of weight 0 are blocks of their own and pool with nothing).
+__device__ __forceinline__ void solve_prompt(const Blocks& bl, const double* wp, int T, int n, double budget,
+                                             double* xp) {
+  __shared__ int next_word;
+  __shared__ int sh_saturated;
+  __shared__ double sh_kappa;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int t = tid; t < n; t += kDesignThreads) {
+    bl.ln[t] = 1;
+    bl.wv[t] = wp[t];
+  }
+  if (tid == 0) next_word = 0;
+  __syncthreads();
+  // (64-bit positions: twice the half length can pass 2^31)
+  for (int64_t half = 1; half < n; half *= 2) {
+    for (int64_t a = 2 * half * tid; a + half < n; a += 2 * half * kDesignThreads)
+      join_blocks(bl, (int)a, (int)(a + half), (int)min(a + 2 * half, (int64_t)n));
+    __syncthreads();
+  }
+  // the sums in the sequential order: blocks taken word by word
+  const int words = (n + 63) / 64;
+  mark_heads(bl, n, 2);
+  __syncthreads();
+  for (;;) {
+    int word = lane == 0 ? atomicAdd(&next_word, 1) : 0;
+    word = __builtin_amdgcn_readfirstlane(word);
+    if (word >= words) break;
+    uint64_t m = bl.heads[word];
+    while (m != 0) {
+      const int s = __builtin_amdgcn_readfirstlane(word * 64 + __builtin_ctzll(m));
+      m &= m - 1;
+      pool_in_order(bl, wp, s, __builtin_amdgcn_readfirstlane(bl.ln[s]));
+    }
+  }
+  __syncthreads();
+  mark_heads(bl, n, 1);
+  __syncthreads();
+  // the block scores sqrt(W_m / L_m)
+  for (int t = tid; t < n; t += kDesignThreads)
+    if (bl.ln[t] > 0) bl.wv[t] = sqrt(bl.wv[t] / (double)bl.ln[t]);
+  __syncthreads();
+  // Suffix sums of L_m s_m (accumulated from the last block), and the first
+  // unsaturated block: kappa(m) = (B - start_m) / sum_{j>=m} L_j s_j with
+  // kappa(m) s_m <= 1.  The first block of weight 0 from which only such blocks
+  // follow (if there is one) is step n: kappa < 0 stands for it.
+  if (wave == 0) {
+    double acc = 0.0, kappa = -1.0;
+    int saturated = n;
+    bool found = n < T;            // false: until a block qualifies, the last block's kappa stands
+    for (int word = words - 1; word >= 0; --word) {
+      const uint64_t heads = bl.heads[word];
+      if (heads == 0) continue;
+      const int t = word * 64 + lane;
+      const bool head = (heads >> lane) & 1;
+      const double score = head ? bl.wv[t] : 0.0;
+      const int len = head ? bl.ln[t] : 0;
+      double rest = 0.0;           // of this lane's block
+      for (uint64_t m = heads; m != 0;) {
+        const int k = 63 - __builtin_clzll(m);
+        m ^= 1ull << k;
+        acc += (double)__builtin_amdgcn_readlane(len, k) * lane_value(score, k);
+        if (lane == k) rest = acc;
+      }
+      const bool none = head && rest == 0.0;
+      const double mine = none ? -1.0 : (budget - (double)t) / rest;
+      const uint64_t ok = __ballot(none || (head && mine * score <= 1.0));
+      if (ok != 0) {
+        const int k = __builtin_ctzll(ok);
+        kappa = lane_value(mine, k);
+        saturated = word * 64 + k;
+        found = true;
+      } else if (!found) {
+        kappa = lane_value(mine, 63 - __builtin_clzll(heads));
+        found = true;
+      }
+    }
+    if (lane == 0) {
+      sh_kappa = kappa;
+      sh_saturated = saturated;
+    }
+  }
+  __syncthreads();
+  const double kappa = sh_kappa;
+  const int saturated = sh_saturated;
+  const double even = (budget - (double)saturated) / (double)(T - saturated);   // used where kappa < 0
+  for (int t = tid; t < T; t += kDesignThreads) {
+    int start = t;                 // of t's block
+    double score = 0.0;
+    if (t < n) {
+      int word = t / 64;
+      uint64_t m = bl.heads[word] & (~0ull >> (63 - (t & 63)));
+      while (m == 0) m = bl.heads[--word];   // step 0 starts a block
+      start = word * 64 + 63 - __builtin_clzll(m);
+      score = bl.wv[start];
+    }
+    const double v = kappa < 0.0 ? (start < saturated ? 1.0 : even) : fmin(1.0, kappa * score);
+    xp[t] = fmax(v, kXiFloor);
+  }
+}
+
+// The sum of the square roots of the weights, by one wave: lane l takes the
+// steps l, l + 64, ... in order, then a fixed butterfly over the lanes.
+__device__ __forceinline__ double root_sum(const double* wp, int T) {
+  double part = 0.0;
+#pragma unroll 8
+  for (int t = threadIdx.x & 63; t < T; t += 64) part += sqrt(wp[t]);
+  return wave_sum(part);
+}
+
+// LDS of a design block: its blocks of steps (12 bytes and a bit per step) when
+// they fit.
+constexpr int kDesignLdsBytes = 156 * 1024;
+constexpr int kDesignLdsSteps = kDesignLdsBytes / 98 * 8;   // 12.25 bytes per step: room for the last word
+
+// One block per prompt: T <= kDesignLdsSteps steps in LDS, otherwise in the workspace.
+__global__ __launch_bounds__(kDesignThreads) void design_cutoffs_kernel(
+    const double* __restrict__ w, const int64_t* __restrict__ xi_off, double budget, int variant, double lambda,
+    double* __restrict__ xi, int32_t* __restrict__ blen, double* __restrict__ bval, int32_t* __restrict__ spare,
+    int32_t* __restrict__ err_flag) {
   __shared__ __attribute__((aligned(16))) unsigned char lds[kDesignLdsBytes];
-  const int p = blockIdx.x;
+  __shared__ int sh_bad, sh_n;
+  __shared__ double sh_root, sh_run[kDesignThreads / 64];
+  const int p = blockIdx.x, tid = threadIdx.x;
   const int64_t a = xi_off[p];
   const int T = (int)(xi_off[p + 1] - a);
   const double* wp = w + a;
   double* xp = xi + a;
   if (variant == PSPO_DESIGN_UNIFORM) {
-    for (int t = threadIdx.x; t < T; t += blockDim.x) xp[t] = (double)(T - t) / (double)T;
+    for (int t = tid; t < T; t += kDesignThreads) xp[t] = (double)(T - t) / (double)T;
     return;
   }
   if (variant == PSPO_DESIGN_TIME_PRIOR) {
-    for (int t = threadIdx.x; t < T; t += blockDim.x) xp[t] = fmax(exp(-lambda * (double)t), kXiFloor);
+    for (int t = tid; t < T; t += kDesignThreads) xp[t] = fmax(exp(-lambda * (double)t), kXiFloor);
     return;
   }
-  const bool w_in_lds = (int64_t)T * 8 <= kDesignLdsBytes;
-  const bool stack_in_lds = (int64_t)T * 20 <= kDesignLdsBytes;
-  double* wl = reinterpret_cast<double*>(lds);
-  bool bad_lane = false;
-  double part = 0.0;   // this lane's steps t = lane, lane + 64, ... in order
-  for (int t = threadIdx.x; t < T; t += 64) {
-    const double v = wp[t];
-    if (w_in_lds) wl[t] = v;
-    if (!(v >= 0.0) || isinf(v)) bad_lane = true;
-    else part += sqrt(v);
-  }
-  const bool bad = __ballot(bad_lane) != 0;
-  const double root_sum = wave_sum(part);   // the lanes' partial sums in a fixed butterfly order
+  // the weights checked, and the last positive one
+  if (tid == 0) sh_bad = sh_n = 0;
   __syncthreads();
-  const double* wr = w_in_lds ? wl : wp;
-  const bool single = bad || budget >= (double)T || root_sum == 0.0 || variant == PSPO_DESIGN_HEURISTIC;
-  if (single && threadIdx.x != 0) return;
-  if (bad) {
-    if (err_flag) atomicOr(err_flag, PSPO_DEVERR_BAD_XI);
-    for (int t = 0; t < T; ++t) xp[t] = NAN;
-    return;
+  int n = 0;
+  bool bad = false;
+  for (int t = tid; t < T; t += kDesignThreads) {
+    const double v = wp[t];
+    if (!(v >= 0.0) || isinf(v)) bad = true;
+    if (v > 0.0) n = t + 1;
   }
-  if (budget >= (double)T) {
-    for (int t = 0; t < T; ++t) xp[t] = 1.0;
-    return;
+  if (bad) atomicOr(&sh_bad, 1);
+  if (n > 0) atomicMax(&sh_n, n);
+  __syncthreads();
+  n = sh_n;
+  double all = -1.0;   // >= 0 or NAN: every step's value
+  if (sh_bad) {
+    if (tid == 0 && err_flag) atomicOr(err_flag, PSPO_DEVERR_BAD_XI);
+    all = NAN;
+  } else if (budget >= (double)T) {
+    all = 1.0;
+  } else if (n == 0) {   // every weight zero: any feasible table is optimal
+    all = budget / (double)T;
   }
-  if (root_sum == 0.0) {   // every weight zero: any feasible table is optimal
-    for (int t = 0; t < T; ++t) xp[t] = budget / (double)T;
+  if (!(all < 0.0)) {
+    for (int t = tid; t < T; t += kDesignThreads) xp[t] = all;
     return;
   }
   if (variant == PSPO_DESIGN_HEURISTIC) {
-    double run = 1.0;
-    for (int t = 0; t < T; ++t) {
-      run = fmin(run, fmin(1.0, budget * sqrt(wr[t]) / root_sum));
-      xp[t] = fmax(run, kXiFloor);
+    // a running minimum: of each wave's 64 steps, then over the waves
+    if (tid < 64) {
+      const double r = root_sum(wp, T);
+      if (tid == 0) sh_root = r;
+    }
+    __syncthreads();
+    const double root = sh_root;
+    double before = 1.0;
+    for (int t0 = 0; t0 < T; t0 += kDesignThreads) {
+      const int t = t0 + tid;
+      double v = t < T ? fmin(1.0, budget * sqrt(wp[t]) / root) : 1.0;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const double u = __shfl_up(v, o);
+        if ((tid & 63) >= o) v = fmin(v, u);
+      }
+      if ((tid & 63) == 63) sh_run[tid >> 6] = v;
+      __syncthreads();
+      double run = before;
+      for (int k = 0; k < kDesignThreads / 64; ++k) {
+        if (k == (tid >> 6)) v = fmin(v, run);
+        run = fmin(run, sh_run[k]);
+      }
+      before = run;
+      if (t < T) xp[t] = fmax(v, kXiFloor);
+      __syncthreads();
     }
     return;
   }
-  // the solve, on LDS-resident weights and stack where they fit
-  if (stack_in_lds)
-    pav_solve(wl, reinterpret_cast<double*>(lds + (int64_t)T * 8), reinterpret_cast<int32_t*>(lds + (int64_t)T * 16),
-              wl, T, budget, xp);
-  else if (w_in_lds)
-    pav_solve(wl, bval + a, blen + a, wl, T, budget, xp);
+  if (T <= kDesignLdsSteps)
+    solve_prompt(Blocks{reinterpret_cast<double*>(lds), reinterpret_cast<int32_t*>(lds + (int64_t)kDesignLdsSteps * 8),
+                        reinterpret_cast<uint64_t*>(lds + (int64_t)kDesignLdsSteps * 12)},
+                 wp, T, n, budget, xp);
   else
-    pav_solve(wp, bval + a, blen + a, xp, T, budget, xp);
+    solve_prompt(Blocks{bval + a, blen + a, reinterpret_cast<uint64_t*>(spare + (a + 1) / 2 * 2)}, wp, T, n, budget,
+                 xp);
 }
 
 // Argument checks shared by the design entry points (host only).
@@ -310,17 +496,17 @@ int check_design_args(const double* w, const int64_t* xi_off, int32_t P, int64_t
   return PSPO_OK;
 }
 
-// The PAV block stack of the prompts whose stack does not fit in LDS (length
-// and summed weight per block, at most one block per step) carved from `ws`
-// (pspo_design_workspace_bytes(total_T), whose first 4 bytes per step are
-// spare), then the solve.  The kernel writes every stack entry before reading
-// it, so the memory needs no clearing.
+// The blocks of the prompts that do not fit in LDS (summed weight, length and
+// the bits of the first steps) carved from `ws`
+// (pspo_design_workspace_bytes(total_T)), then the solve.  The kernel writes
+// every entry before reading it, so the memory needs no clearing.
 int launch_design(const double* w, const int64_t* xi_off, int32_t P, int64_t total_T, double budget, int32_t variant,
                   double lambda, double* xi, char* ws, int32_t* err_flag, hipStream_t stream) {
   int32_t* blen = reinterpret_cast<int32_t*>(ws + round_up(total_T * 4, 256));
   double* bval = reinterpret_cast<double*>(ws + 2 * round_up(total_T * 4, 256));
-  hipLaunchKernelGGL(design_cutoffs_kernel, dim3((unsigned)P), dim3(64), 0, stream, w, xi_off, budget, variant,
-                     lambda, xi, blen, bval, err_flag);
+  int32_t* spare = reinterpret_cast<int32_t*>(ws);
+  hipLaunchKernelGGL(design_cutoffs_kernel, dim3((unsigned)P), dim3(kDesignThreads), 0, stream, w, xi_off, budget,
+                     variant, lambda, xi, blen, bval, spare, err_flag);
   PSPO_LAUNCHED("design_cutoffs_kernel", stream);
   return PSPO_OK;
 }
