@@ -40,17 +40,56 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// One wave per (prompt, step); 4 waves per block.
-__global__ __launch_bounds__(256) void design_weights_kernel(
+// Sum over groups of G consecutive lanes (all lanes active; every lane of a
+// group gets it): lane exchanges inside 16-lane rows as DPP moves.
+template <int kCtrl>
+__device__ __forceinline__ double dpp(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, kCtrl, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), kCtrl, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+template <int G>
+__device__ __forceinline__ double group_sum(double v) {
+  static_assert(G >= 4 && G <= 64, "groups of 4 to 64 lanes");
+  v += dpp<0xB1>(v);                      // lane ^ 1
+  v += dpp<0x4E>(v);                      // lane ^ 2
+  if constexpr (G >= 8) v += dpp<0x141>(v);    // the other quad of the half row (mirrored)
+  if constexpr (G >= 16) v += dpp<0x140>(v);   // the other half of the row (mirrored)
+  if constexpr (G >= 32) v += __shfl_xor(v, 16);
+  if constexpr (G >= 64) v += __shfl_xor(v, 32);
+  return v;
+}
+
+// The weights: a group of G lanes (a power of two >= topk, up to 64) per
+// (prompt, step), 64 / G steps per one-wave block.  The completions are taken
+// in order; each entry of a completion's list finds its token id's slot in a
+// hash table of the step in LDS (open addressing, at most half full) and adds
+// its signed probability there, so every id's terms are added in the order of the
+// completions; the next completion's entries are read one ahead.  One wave per step
+// compared every entry with every other one from LDS, and 8 of its lanes summed
+// the lists' masses with an exp per entry of their own: 160 us for 35,000
+// steps of 8 top-16 lists (19 MB of lists), 28 us now.
+template <int G>
+__global__ __launch_bounds__(64) void design_weights_kernel(
     const float* __restrict__ gamma, const int32_t* __restrict__ topk_ids, const float* __restrict__ topk_logp,
     int topk, const int32_t* __restrict__ lengths, const int32_t* __restrict__ full_off,
-    const float* __restrict__ rewards, const int64_t* __restrict__ xi_off, int P, int K, int64_t total,
+    const float* __restrict__ rewards, const int64_t* __restrict__ xi_off, int P, int K, int64_t total, int slots,
     double* __restrict__ w, double* __restrict__ gbar_out, double* __restrict__ u_out, int32_t* __restrict__ err_flag) {
-  __shared__ int32_t sid[4][kDesignMaxEntries];
-  __shared__ double sval[4][kDesignMaxEntries];
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t g = (int64_t)blockIdx.x * 4 + wv;
-  const bool live = g < total;   // a wave past the end still takes part in the barrier
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  constexpr int kSteps = 64 / G;
+  const int lane = threadIdx.x, e = lane % G;
+  double* all_sums = reinterpret_cast<double*>(lds);                       // [steps][slots]
+  int32_t* all_ids = reinterpret_cast<int32_t*>(lds + (int64_t)kSteps * slots * 8);
+  for (int i = lane; i < kSteps * slots; i += 64) {
+    all_sums[i] = 0.0;
+    all_ids[i] = -1;
+  }
+  double* sums = all_sums + lane / G * slots;
+  int32_t* ids = all_ids + lane / G * slots;
+  const int shift = __builtin_clz(slots) + 1;   // a hash's top log2(slots) bits
+  const int64_t g = (int64_t)blockIdx.x * kSteps + lane / G;
+  const bool live = g < total;
   // prompt of g: the last p with xi_off[p] <= g
   int lo = 0, hi = P - 1;
   while (live && lo < hi) {
@@ -60,56 +99,77 @@ __global__ __launch_bounds__(256) void design_weights_kernel(
   }
   const int p = lo;
   const int t = live ? (int)(g - xi_off[p]) + 1 : 0;
+  __syncthreads();
 
-  // per-entry signed probabilities of the alive completions (0 for the others)
-  const int ne = live ? K * topk : 0;
-  for (int j = lane; j < ne; j += 64) {
-    const int k = j / topk, r = p * K + k;
-    int32_t id = -1;
-    double v = 0.0;
-    if (lengths[r] >= t) {
-      const int64_t row = (int64_t)full_off[r] + t - 1;
-      id = topk_ids[row * topk + (j - k * topk)];
-      v = exp((double)topk_logp[row * topk + (j - k * topk)]) * (rewards[r] > 0.5f ? 1.0 : -1.0);
+  double rest = 0.0, gsum = 0.0, nalive = 0.0, nsucc = 0.0;
+  for (int k0 = 0; k0 < K; k0 += G) {
+    // lane e: the row of completion k0 + e at this step (-1: not alive) and its sign
+    int64_t row = -1;
+    bool succ = false;
+    if (live && k0 + e < K) {
+      const int r = p * K + k0 + e;
+      if (lengths[r] >= t) {
+        row = (int64_t)full_off[r] + t - 1;
+        succ = rewards[r] > 0.5f;
+        gsum += (double)gamma[row];
+        nalive += 1.0;
+        nsucc += succ ? 1.0 : 0.0;
+      }
     }
-    sid[wv][j] = id;
-    sval[wv][j] = v;
+    const int kn = min(G, K - k0);
+    int64_t cur = __shfl(row, 0, G);
+    int32_t id_next = -1;
+    float lp_next = 0.f;
+    if (cur >= 0 && e < topk) {
+      id_next = topk_ids[cur * topk + e];
+      lp_next = topk_logp[cur * topk + e];
+    }
+    for (int k = 0; k < kn; ++k) {
+      const int64_t now = cur;
+      int32_t id = id_next;
+      float lp = lp_next;
+      cur = k + 1 < kn ? __shfl(row, k + 1, G) : (int64_t)-1;
+      if (cur >= 0 && e < topk) {
+        id_next = topk_ids[cur * topk + e];
+        lp_next = topk_logp[cur * topk + e];
+      }
+      const double sign = __shfl((int)succ, k, G) ? 1.0 : -1.0;
+      double mass = 0.0;
+      if (now >= 0) {
+        for (int e1 = e;;) {
+          if (e1 < topk) {
+            const double pr = exp((double)lp);
+            mass += pr;
+            if (id >= 0) {
+              int slot = (int)((uint32_t)id * 0x9E3779B1u >> shift);
+              for (;;) {           // ends: the table has more slots than entries
+                const int32_t old = atomicCAS(&ids[slot], -1, id);
+                if (old == -1 || old == id) break;
+                slot = (slot + 1) & (slots - 1);
+              }
+              unsafeAtomicAdd(&sums[slot], sign * pr);   // (one row's ids may repeat)
+            }
+          }
+          e1 += G;
+          if (e1 - e >= topk) break;
+          if (e1 < topk) {         // lists longer than a wave
+            id = topk_ids[now * topk + e1];
+            lp = topk_logp[now * topk + e1];
+          }
+        }
+      }
+      mass = group_sum<G>(mass);
+      if (now >= 0) rest += sign * fmax(0.0, 1.0 - mass);
+    }
   }
   __syncthreads();
-  // each distinct token id is summed once, by the lane that holds its first occurrence
   double l1 = 0.0;
-  for (int j = lane; j < ne; j += 64) {
-    const int32_t id = sid[wv][j];
-    if (id < 0) continue;
-    bool first = true;
-    for (int i = 0; i < j && first; ++i) first = sid[wv][i] != id;
-    if (!first) continue;
-    double s = 0.0;
-    for (int i = j; i < ne; ++i)
-      if (sid[wv][i] == id) s += sval[wv][i];
-    l1 += fabs(s);
-  }
-  // per completion: the mass outside its top-k, and its gamma
-  double rest = 0.0, gsum = 0.0, nalive = 0.0, nsucc = 0.0;
-  if (live && lane < K) {
-    const int r = p * K + lane;
-    if (lengths[r] >= t) {
-      const int64_t row = (int64_t)full_off[r] + t - 1;
-      double mass = 0.0;
-      for (int e = 0; e < topk; ++e) mass += exp((double)topk_logp[row * topk + e]);
-      const bool ok = rewards[r] > 0.5f;
-      rest = fmax(0.0, 1.0 - mass) * (ok ? 1.0 : -1.0);
-      gsum = (double)gamma[row];
-      nalive = 1.0;
-      nsucc = ok ? 1.0 : 0.0;
-    }
-  }
-  l1 = wave_sum(l1);
-  rest = wave_sum(rest);
-  gsum = wave_sum(gsum);
-  nalive = wave_sum(nalive);
-  nsucc = wave_sum(nsucc);
-  if (live && lane == 0) {
+  for (int i = e; i < slots; i += G) l1 += fabs(sums[i]);
+  l1 = group_sum<G>(l1);
+  gsum = group_sum<G>(gsum);
+  nalive = group_sum<G>(nalive);
+  nsucc = group_sum<G>(nsucc);
+  if (live && e == 0) {
     if (nalive == 0.0) {   // the table is longer than every completion of the prompt
       if (err_flag) atomicOr(err_flag, PSPO_DEVERR_BAD_XI);
       w[g] = NAN;
@@ -126,10 +186,22 @@ __global__ __launch_bounds__(256) void design_weights_kernel(
   }
 }
 
+// Groups of G lanes: the smallest power of two >= topk (at least 4, at most 64)
+// whose 64 / G tables stay within 24 KB of LDS, so that six blocks or more share a CU.
+struct WeightsShape {
+  int group, slots;
+};
+WeightsShape weights_shape(int K, int topk) {
+  WeightsShape s{4, 16};
+  while (s.slots < 2 * K * topk) s.slots *= 2;   // <= 512
+  while (s.group < 64 && (s.group < topk || 64 / s.group * s.slots * 12 > 24 * 1024)) s.group *= 2;
+  return s;
+}
+
 // The budgeted monotone solve (App. F).  One thread per prompt ran Pooling
 // Adjacent Violators over the steps, one dependent chain of LDS accesses and
 // branches per step, and then summed, searched and wrote the table alone:
-// 1,922 us for 8 prompts of 2,500 to 6,900 steps, 293 us with what follows.
+// 1,922 us for 8 prompts of 2,500 to 6,900 steps, 230 to 290 us with what follows.
 //
 // The blocks are found first, by all threads: blocks of steps are merged pairwise
 // up a tree, where only the blocks at the joint can violate, and pooling adjacent
@@ -565,10 +637,19 @@ int pspo_design_weights(const float* gamma, const int32_t* topk_ids, const float
   PSPO_REQUIRE(aligned(w, 8) && aligned(gamma_bar, 8) && aligned(u, 8) && aligned(xi_off, 8), PSPO_ERR_INVALID_ARG,
                "misaligned float64 / int64 pointer");
   if (int rc = require_gfx950()) return rc;
-  const int64_t blocks = (total_T + 3) / 4;
-  PSPO_REQUIRE(blocks <= INT32_MAX, PSPO_ERR_UNSUPPORTED, "problem too large");
-  hipLaunchKernelGGL(design_weights_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, gamma, topk_ids, topk_logp,
-                     topk, lengths, full_off, rewards, xi_off, P, K, total_T, w, gamma_bar, u, err_flag);
+  PSPO_REQUIRE((total_T + 3) / 4 <= INT32_MAX, PSPO_ERR_UNSUPPORTED, "problem too large");
+  const WeightsShape shape = weights_shape(K, topk);
+  const int steps = 64 / shape.group;
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((total_T + steps - 1) / steps)), dim3(64),
+                       (unsigned)(steps * shape.slots * 12), stream, gamma, topk_ids, topk_logp, topk, lengths,
+                       full_off, rewards, xi_off, P, K, total_T, shape.slots, w, gamma_bar, u, err_flag);
+  };
+  if (shape.group == 4) launch(design_weights_kernel<4>);
+  else if (shape.group == 8) launch(design_weights_kernel<8>);
+  else if (shape.group == 16) launch(design_weights_kernel<16>);
+  else if (shape.group == 32) launch(design_weights_kernel<32>);
+  else launch(design_weights_kernel<64>);
   PSPO_LAUNCHED("design_weights_kernel", stream);
   return PSPO_OK;
 }
