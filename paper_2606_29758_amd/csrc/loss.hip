@@ -131,15 +131,11 @@ __device__ __forceinline__ void store_kept_f16(const AccTile& acc, const float* 
 // per-column softmax partials of each 384-row vocabulary tile.  (The target
 // logits come from row_dots_kernel: picking one accumulator per column out
 // of the 48 a lane holds costs a compare and a select for each of them.)
-// kFull: every row of every tile is a token id (no per-row mask); otherwise
-// the launch is the partial last vocabulary tile, tm0 its index (the product's
-// row tile 0).  Two instantiations rather than a branch in one: with a branch
-// the compiler spills accumulators.
-template <bool kFull>
+// Rows past V are -inf (kMaskRows): they raise no maximum and add 0.
 struct EpiForward {
-  int V, N;
+  static constexpr bool kMaskRows = true;
+  int N;
   int64_t ldp;  // stride between vocabulary tiles in the partial arrays (= Npad)
-  int tm0;
   float* part_m;
   float* part_l;
   const int32_t* n_dev;
@@ -147,17 +143,15 @@ struct EpiForward {
   int kept_tiles;        //   per tile (tm, tn) a block at (tm * kept_cols + tn) * 384 * 256
   int kept_cols;         //   (store_kept_f16)
 
-  __device__ __forceinline__ void apply(const AccTile& acc, int tm_launch, int tn, int wm, int wn, int lane,
+  __device__ __forceinline__ void apply(const AccTile& acc, int tm, int tn, int wm, int wn, int lane,
                                         float* smem) const {
     float* red = smem;  // [2 wave rows][256 columns][m, l]
-    const int tm = kFull ? tm_launch : tm0 + tm_launch;
     const int n = min(N, __builtin_amdgcn_readfirstlane(*n_dev));
-    const int vbase = tm * kTileM + acc_row(wm, 0, 0, lane);   // this lane's rows: vbase + i*16 + r
 #pragma unroll
     for (int j = 0; j < kBlocksN; ++j) {
       const int cl = acc_col(wn, j, lane);
-      // the lane's 48 values of column j (q = 4 i + r: row vbase + 16 i + r),
-      // the AGPR ones read once into VGPRs for both passes below
+      // the lane's 48 values of column j (q = 4 i + r: its row 16 i + r), the
+      // AGPR ones read once into VGPRs for both passes below
       float xs[kBlocksM * kAccPerBlock];
 #pragma unroll
       for (int q = 0; q < kBlocksM * kAccPerBlock; ++q) {
@@ -167,44 +161,24 @@ struct EpiForward {
           xs[q] = acc.v[(q >> 2) - kBlocksAgpr][j][q & 3];
       }
       auto x = [&](int q) { return xs[q]; };
-      float m, l;
-      if constexpr (kFull) {
-        // every row is a token id: three-input maxima (no per-value select),
-        // exp2(z log2e - m log2e) as one fma + exp, four partial sums
-        float mm[4];
+      // three-input maxima (no per-value select), exp2(z log2e - m log2e) as one
+      // fma + exp, four partial sums.  A wave whose rows all lie past V has
+      // m = -inf and an l of NaN, which the join below leaves out.
+      float mm[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) mm[k] = max3(x(k), x(k + 4), x(k + 8));
+      for (int k = 0; k < 4; ++k) mm[k] = max3(x(k), x(k + 4), x(k + 8));
 #pragma unroll
-        for (int q = 12; q < kBlocksM * kAccPerBlock; q += 8)
+      for (int q = 12; q < kBlocksM * kAccPerBlock; q += 8)
 #pragma unroll
-          for (int k = 0; k < 4; ++k) mm[k] = max3(mm[k], x(q + k), x(q + k + 4));
-        m = max3(mm[0], mm[1], max3(mm[2], mm[3], mm[3]));
-        m = fmaxf(m, __shfl_xor(m, 16));
-        m = fmaxf(m, __shfl_xor(m, 32));
-        const float mb = m * kLog2e;
-        float ls[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int k = 0; k < 4; ++k) mm[k] = max3(mm[k], x(q + k), x(q + k + 4));
+      float m = max3(mm[0], mm[1], max3(mm[2], mm[3], mm[3]));
+      m = fmaxf(m, __shfl_xor(m, 16));
+      m = fmaxf(m, __shfl_xor(m, 32));
+      const float mb = m * kLog2e;
+      float ls[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int q = 0; q < kBlocksM * kAccPerBlock; ++q) ls[q & 3] += __builtin_amdgcn_exp2f(fmaf(x(q), kLog2e, -mb));
-        l = (ls[0] + ls[1]) + (ls[2] + ls[3]);
-      } else {
-        m = kNegInf;
-#pragma unroll
-        for (int i = 0; i < kBlocksM; ++i)
-#pragma unroll
-          for (int r = 0; r < kAccPerBlock; ++r)
-            if (vbase + i * 16 + r < V) m = fmaxf(m, x(i * kAccPerBlock + r));
-        m = fmaxf(m, __shfl_xor(m, 16));
-        m = fmaxf(m, __shfl_xor(m, 32));
-        l = 0.f;
-        if (m != kNegInf) {
-          const float mb = m * kLog2e;
-#pragma unroll
-          for (int i = 0; i < kBlocksM; ++i)
-#pragma unroll
-            for (int r = 0; r < kAccPerBlock; ++r)
-              if (vbase + i * 16 + r < V) l += __builtin_amdgcn_exp2f(fmaf(x(i * kAccPerBlock + r), kLog2e, -mb));
-        }
-      }
+      for (int q = 0; q < kBlocksM * kAccPerBlock; ++q) ls[q & 3] += __builtin_amdgcn_exp2f(fmaf(x(q), kLog2e, -mb));
+      float l = (ls[0] + ls[1]) + (ls[2] + ls[3]);
       l += __shfl_xor(l, 16);
       l += __shfl_xor(l, 32);
       if (lane < 16) {
@@ -279,12 +253,10 @@ __device__ __forceinline__ u32x2 quad_transpose(u32x2 p, int k) {
 //   * vocabulary-major: a 4 x 4 transpose inside each quad of lanes gives a
 //     lane 4 consecutive tokens of one row; exchanging with the quad 4 lanes
 //     away (DPP row shift) between the two column blocks gives it 8.
-// kFull: every row of every tile is a token id (no per-row mask; the only kind
-// when V is a multiple of 384); otherwise the launch is the partial last
-// vocabulary tile, tm0 its chunk row tile (the product's row tile 0).
-template <bool kFull>
+// Rows past V are -inf (kMaskRows): their gradient is 0.
 struct EpiDelta {
-  int V, N, v0, tm0;
+  static constexpr bool kMaskRows = true;
+  int N;
   // Both layouts row-blocked, so that each tile's values sit in a compact
   // region (the vocabulary-major one a contiguous 192 KB block):
   uint16_t* dT;          // [Vc/384][tkb][384][32]: rows = vocabulary entries (block = vocabulary tile), K = tokens
@@ -295,11 +267,11 @@ struct EpiDelta {
   const float* cdelta;
   const int32_t* n_dev;
 
-  __device__ __forceinline__ void apply(AccTile& acc, int tm_launch, int tn, int wm, int wn, int lane, float*) const {
+  __device__ __forceinline__ void apply(AccTile& acc, int tm, int tn, int wm, int wn, int, float*) const {
+    // the lane index, recomputed here: otherwise the compiler keeps values
+    // derived from the kernel's copy live across the product loop and spills one
+    const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     const int n = min(N, __builtin_amdgcn_readfirstlane(*n_dev));
-    const int tm = kFull ? tm_launch : tm0 + tm_launch;
-    const int vl0 = tm * kTileM + acc_row(wm, 0, 0, lane);   // chunk rows of this lane: vl0 + i*16 + r
-    [[maybe_unused]] const int vbase = v0 + vl0;   // (rows past V of a partial last tile are masked)
     // per-column token data of the lane's 8 columns, fetched together (one
     // round trip: the arrays are in column order)
     float cc[kBlocksN];
@@ -347,10 +319,7 @@ struct EpiDelta {
             const int i = 2 * ip + ii, j = 2 * jp + jj;
             float x[kAccPerBlock];
 #pragma unroll
-            for (int r = 0; r < kAccPerBlock; ++r) {
-              x[r] = grad_mag(acc_get(acc, i, j, r), cc[j]);
-              if constexpr (!kFull) x[r] = (vbase + i * 16 + r < V) ? x[r] : 0.f;
-            }
+            for (int r = 0; r < kAccPerBlock; ++r) x[r] = grad_mag(acc_get(acc, i, j, r), cc[j]);
             blk[ii][jj].x = pack_bf16x2(x[0], x[1]) ^ sg[j];
             blk[ii][jj].y = pack_bf16x2(x[2], x[3]) ^ sg[j];
           }
@@ -501,6 +470,7 @@ __global__ __launch_bounds__(256) void zero_targets_kernel(int N, const int32_t*
 // fence between the blocks): hoisting every load of the tile would need 384
 // more registers.
 struct EpiDW {
+  static constexpr bool kMaskRows = false;
   int V, d, v0;
   float* dW;
   bool accumulate;
@@ -542,6 +512,7 @@ struct EpiDW {
 // After the first vocabulary chunk each row block's old values are loaded,
 // added and stored before the next block's loads (see EpiDW).
 struct EpiDH {
+  static constexpr bool kMaskRows = false;
   int N, d;
   float* dH;
   bool first;
@@ -1412,25 +1383,16 @@ int pspo_loss_fwd_bwd(const uint16_t* hidden, const uint16_t* w_head, const int3
   hipLaunchKernelGGL(kblock_rows_kernel, dim3(ctiles64, (unsigned)(pl.Npad / 32)), dim3(256), 0, stream, hidden,
                      (int64_t)d, d, N, fwd_idx, n_fwd, hk, pl.Npad, nullptr, (int64_t)0, (int64_t)kTileK);
   PSPO_LAUNCHED("kblock_rows_kernel", stream);
-  // 2. forward logits -> per-tile softmax partials (target logits apart): the
-  //    vocabulary tiles whose rows are all token ids, then a partial last one
+  // 2. forward logits -> per-tile softmax partials (target logits apart)
   {
     ProductTimer timer(stream);
     if (int rc = timer.begin(PSPO_TIME_FORWARD)) return rc;
-    const int tiles_full = V / kTileM, kept_tiles = zk != nullptr ? (int)(pl.Vc / kTileM) : 0;
-    if (tiles_full > 0) {
-      // the kept tiles' stores spread over the XCDs
-      GemmShape g{wk, pl.Vpad, tiles_full * kTileM, hk, pl.Npad, N, Dk, tiles_full, tiles_tok_n, n_fwd, kDynN,
-                  kept_tiles < tiles_full ? kept_tiles : tiles_full};
-      EpiForward<true> e{V, N, pl.Npad, 0, part_m, part_l, n_fwd, zk, kept_tiles, tiles_tok_n};
-      if (int rc = launch_gemm(g, e, stream)) return rc;
-    }
-    if (tiles_full < tiles_voc) {
-      GemmShape g{wk + (int64_t)tiles_full * kTileM * kTileK, pl.Vpad, V - tiles_full * kTileM, hk, pl.Npad, N, Dk, 1,
-                  tiles_tok_n, n_fwd, kDynN};
-      EpiForward<false> e{V, N, pl.Npad, tiles_full, part_m, part_l, n_fwd, zk, kept_tiles, tiles_tok_n};
-      if (int rc = launch_gemm(g, e, stream)) return rc;
-    }
+    const int kept_tiles = zk != nullptr ? (int)(pl.Vc / kTileM) : 0;
+    // the kept tiles' stores spread over the XCDs
+    GemmShape g{wk, pl.Vpad, V, hk, pl.Npad, N, Dk, tiles_voc, tiles_tok_n, n_fwd, kDynN,
+                kept_tiles < tiles_voc ? kept_tiles : tiles_voc};
+    EpiForward e{N, pl.Npad, part_m, part_l, n_fwd, zk, kept_tiles, tiles_tok_n};
+    if (int rc = launch_gemm(g, e, stream)) return rc;
     if (int rc = timer.end()) return rc;
   }
   // the target logit of each forward column (the column's token row and target)
@@ -1473,22 +1435,10 @@ int pspo_loss_fwd_bwd(const uint16_t* hidden, const uint16_t* w_head, const int3
                          act_delta, dN, pl.Vc / kTileK, dT, pl.Npad / kTileK);
       PSPO_LAUNCHED("logit_grad_kept_kernel", stream);
     } else {
-      // the chunk's vocabulary tiles whose rows are all token ids, then a
-      // partial last one (the last chunk's, when 384 does not divide V)
-      const int64_t rows = (V - v0) < vc ? (V - v0) : vc;
-      const int tfull = (int)(rows / kTileM);
-      if (tfull > 0) {
-        GemmShape g{wk + v0 * kTileK, pl.Vpad, tfull * kTileM, hk, pl.Npad, N, Dk, tfull, tiles_tok_n, n_act, kDynN};
-        EpiDelta<true> e{V, N, (int)v0, 0, dT, pl.Npad / kTileK, dN, pl.Vc / kTileK, act_lse, act_delta, n_act};
-        if (int rc = launch_gemm(g, e, stream)) return rc;
-      }
-      if (tfull < ctiles) {
-        const int64_t vp = v0 + (int64_t)tfull * kTileM;   // first row of the partial tile
-        GemmShape g{wk + vp * kTileK, pl.Vpad, (int)(V - vp), hk, pl.Npad, N, Dk, 1, tiles_tok_n, n_act, kDynN};
-        EpiDelta<false> e{V, N, (int)v0, tfull, dT, pl.Npad / kTileK, dN, pl.Vc / kTileK, act_lse, act_delta,
-                          n_act};
-        if (int rc = launch_gemm(g, e, stream)) return rc;
-      }
+      GemmShape g{wk + v0 * kTileK, pl.Vpad, (int)((V - v0) < vc ? (V - v0) : vc), hk, pl.Npad, N, Dk, ctiles,
+                  tiles_tok_n, n_act, kDynN};
+      EpiDelta e{N, dT, pl.Npad / kTileK, dN, pl.Vc / kTileK, act_lse, act_delta, n_act};
+      if (int rc = launch_gemm(g, e, stream)) return rc;
     }
     if (int rc = t_grad.end()) return rc;
     hipLaunchKernelGGL(zero_targets_kernel, dim3((unsigned)std::min<int64_t>((pl.Npad + 255) / 256, 1024)), dim3(256),

@@ -37,27 +37,22 @@ constexpr float kNegInf = -INFINITY;
 // column's target.  (The target logits come from row_dots_kernel: picking one
 // accumulator per column out of the 48 a lane holds costs a compare and a
 // select for each of them.)
-// kFull: every row of every tile is a token id (no per-row mask); otherwise
-// the launch is the partial last vocabulary tile, tm0 its index.  Two
-// instantiations rather than a branch in one: with a branch the compiler
-// spills accumulators.
-template <bool kFull>
+// Rows past V are -inf (kMaskRows): they raise no maximum and add 0.
 struct EpiProxy {
-  int V, N;
+  static constexpr bool kMaskRows = true;
+  int N;
   int64_t ldp;  // stride between vocabulary tiles in the partial arrays (= Npad)
-  int tm0;
   const int32_t* target;
   float* part_m;
   float* part_s1;
   float* part_s2;
 
-  __device__ __forceinline__ void apply(const AccTile& acc, int tm_launch, int tn, int wm, int wn, int,
+  __device__ __forceinline__ void apply(const AccTile& acc, int tm, int tn, int wm, int wn, int,
                                         float* smem) const {
     float* red = smem;  // [2 wave rows][256 columns][m, S1, S2]
     // the lane index, recomputed here: otherwise the compiler keeps values
     // derived from the kernel's copy live across the product loop and spills one
     const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-    const int tm = kFull ? tm_launch : tm0 + tm_launch;
     const int vbase = tm * kTileM + acc_row(wm, 0, 0, lane);   // this lane's rows: vbase + i*16 + r
     // the targets of the lane's 8 columns, fetched together
     int tgts[kBlocksN];
@@ -83,56 +78,31 @@ struct EpiProxy {
           xs[q] = acc.v[(q >> 2) - kBlocksAgpr][j][q & 3];
       }
       auto x = [&](int q) { return xs[q]; };
-      float m, s1, s2;
-      if constexpr (kFull) {
-        // every row is a token id: three-input maxima, exp2(z log2e - m log2e)
-        // as one fma + exp, the target's own entry selected away, four
-        // partial sums of each kind
-        float mm[4];
+      // three-input maxima, exp2(z log2e - m log2e) as one fma + exp, the
+      // target's own entry selected away, four partial sums of each kind.  A wave
+      // whose rows all lie past V has m = -inf and sums of NaN, which the join
+      // below leaves out.
+      float mm[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) mm[k] = max3(x(k), x(k + 4), x(k + 8));
+      for (int k = 0; k < 4; ++k) mm[k] = max3(x(k), x(k + 4), x(k + 8));
 #pragma unroll
-        for (int q = 12; q < kBlocksM * kAccPerBlock; q += 8)
+      for (int q = 12; q < kBlocksM * kAccPerBlock; q += 8)
 #pragma unroll
-          for (int k = 0; k < 4; ++k) mm[k] = max3(mm[k], x(q + k), x(q + k + 4));
-        m = max3(mm[0], mm[1], max3(mm[2], mm[3], mm[3]));
-        m = fmaxf(m, __shfl_xor(m, 16));
-        m = fmaxf(m, __shfl_xor(m, 32));
-        const float mb = m * kLog2e;
-        float a1[4] = {0.f, 0.f, 0.f, 0.f}, a2[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int k = 0; k < 4; ++k) mm[k] = max3(mm[k], x(q + k), x(q + k + 4));
+      float m = max3(mm[0], mm[1], max3(mm[2], mm[3], mm[3]));
+      m = fmaxf(m, __shfl_xor(m, 16));
+      m = fmaxf(m, __shfl_xor(m, 32));
+      const float mb = m * kLog2e;
+      float a1[4] = {0.f, 0.f, 0.f, 0.f}, a2[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int q = 0; q < kBlocksM * kAccPerBlock; ++q) {
-          float e = __builtin_amdgcn_exp2f(fmaf(x(q), kLog2e, -mb));
-          e = vbase + (q >> 2) * 16 + (q & 3) != tgt ? e : 0.f;
-          a1[q & 3] += e;
-          a2[q & 3] = fmaf(e, e, a2[q & 3]);
-        }
-        s1 = (a1[0] + a1[1]) + (a1[2] + a1[3]);
-        s2 = (a2[0] + a2[1]) + (a2[2] + a2[3]);
-      } else {
-        m = kNegInf;
-#pragma unroll
-        for (int i = 0; i < kBlocksM; ++i)
-#pragma unroll
-          for (int r = 0; r < kAccPerBlock; ++r)
-            if (vbase + i * 16 + r < V) m = fmaxf(m, x(i * kAccPerBlock + r));
-        m = fmaxf(m, __shfl_xor(m, 16));
-        m = fmaxf(m, __shfl_xor(m, 32));
-        s1 = 0.f;
-        s2 = 0.f;
-        if (m != kNegInf) {
-#pragma unroll
-          for (int i = 0; i < kBlocksM; ++i)
-#pragma unroll
-            for (int r = 0; r < kAccPerBlock; ++r) {
-              const int v = vbase + i * 16 + r;
-              // the target's own entry is left out (selected away, not subtracted)
-              const float e = (v < V && v != tgt) ? __expf(x(i * kAccPerBlock + r) - m) : 0.f;
-              s1 += e;
-              s2 += e * e;
-            }
-        }
+      for (int q = 0; q < kBlocksM * kAccPerBlock; ++q) {
+        float e = __builtin_amdgcn_exp2f(fmaf(x(q), kLog2e, -mb));
+        e = vbase + (q >> 2) * 16 + (q & 3) != tgt ? e : 0.f;
+        a1[q & 3] += e;
+        a2[q & 3] = fmaf(e, e, a2[q & 3]);
       }
+      float s1 = (a1[0] + a1[1]) + (a1[2] + a1[3]);
+      float s2 = (a2[0] + a2[1]) + (a2[2] + a2[3]);
       s1 += __shfl_xor(s1, 16);
       s1 += __shfl_xor(s1, 32);
       s2 += __shfl_xor(s2, 16);
@@ -290,25 +260,12 @@ int pspo_score_proxy(const uint16_t* hidden, const uint16_t* w_head, const int32
                      (int64_t)d, d, N, nullptr, nullptr, hk, pl.Npad, nullptr, (int64_t)0, (int64_t)kTileK);
   PSPO_LAUNCHED("kblock_rows_kernel", stream);
   {
-    // the vocabulary tiles whose rows are all token ids, then a partial last one
     ProductTimer timer(stream);
     if (int rc = timer.begin(PSPO_TIME_PROXY)) return rc;
-    const int tiles_full = V / kTileM;
-    if (tiles_full > 0) {
-      GemmShape g{wk, pl.Vpad, tiles_full * kTileM, hk, pl.Npad, N, Dk, tiles_full, tiles_tok};
-      EpiProxy<true> e{V, N, pl.Npad, 0, target, part_m, part_s1, part_s2};
-      hipLaunchKernelGGL(gemm_nt_kernel<EpiProxy<true>>, dim3(gemm_grid(tiles_full, tiles_tok)), dim3(kGemmThreads),
-                         0, stream, g, e);
-      PSPO_LAUNCHED("gemm_nt_kernel (score proxy)", stream);
-    }
-    if (tiles_full < tiles_voc) {
-      GemmShape g{wk + (int64_t)tiles_full * kTileM * kTileK, pl.Vpad, V - tiles_full * kTileM, hk, pl.Npad, N, Dk, 1,
-                  tiles_tok};
-      EpiProxy<false> e{V, N, pl.Npad, tiles_full, target, part_m, part_s1, part_s2};
-      hipLaunchKernelGGL(gemm_nt_kernel<EpiProxy<false>>, dim3(gemm_grid(1, tiles_tok)), dim3(kGemmThreads), 0,
-                         stream, g, e);
-      PSPO_LAUNCHED("gemm_nt_kernel (score proxy)", stream);
-    }
+    GemmShape g{wk, pl.Vpad, V, hk, pl.Npad, N, Dk, tiles_voc, tiles_tok};
+    hipLaunchKernelGGL(gemm_nt_kernel<EpiProxy>, dim3(gemm_grid(tiles_voc, tiles_tok)), dim3(kGemmThreads), 0, stream,
+                       g, EpiProxy{N, pl.Npad, target, part_m, part_s1, part_s2});
+    PSPO_LAUNCHED("gemm_nt_kernel (score proxy)", stream);
     if (int rc = timer.end()) return rc;
   }
   // the target logit and ||h||^2 of every token, one pass over its hidden row
