@@ -463,54 +463,83 @@ __global__ __launch_bounds__(256) void zero_targets_kernel(int N, const int32_t*
   }
 }
 
+// A wave's 192 x 128 part of a product written to rows of float32, one block of
+// 16 rows at a time through the wave's own LDS, so that each store (and, where the
+// rows are added to, each load, kAhead blocks ahead) moves 16 bytes per lane and
+// whole 512-byte pieces of two rows.  `row(r)`: the output row (d floats each,
+// from `base` on) of the wave's row r, or -1; columns col0 .. of it are written,
+// as far as they exist (d % 8 == 0).  Straight from
+// the accumulators a store moved 4 bytes per lane in 64-byte pieces of four rows,
+// and adding waited for a batch of such loads before each batch of stores.  With the dW product launched whole
+// where its K is short (launch_gemm_split_tail): 200 tokens on the 7B-shaped head
+// (2.2 GB of dW written) 3,366 -> 2,450 us a call, 2,048 tokens that add to dW
+// 8,510 -> 7,391 us.
+template <class Row>
+__device__ __forceinline__ void write_wave_rows(const AccTile& acc, int wave, float* smem, float* base, int d,
+                                                int col0, bool add, const Row& row) {
+  constexpr int kLdsRowF = kWaveN + 4;   // the four row groups of a write hit distinct banks
+  constexpr int kAhead = 2, kPieces = 8;
+  // (recomputed: the kernel's copy would stay live across the product loop)
+  const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  float* sh = smem + wave * 16 * kLdsRowF;
+  float* put = sh + (lane >> 4) * 4 * kLdsRowF + (lane & 15);
+  // this lane's piece q of row block i: row 16 i + 2 q + lane / 32, 4 columns
+  const int hr = lane >> 5, c = (lane & 31) * 4;
+  const float* get = sh + hr * kLdsRowF + c;
+  const bool on = col0 + c < d;
+  unsigned char* out = reinterpret_cast<unsigned char*>(base + col0 + c);
+  auto place = [&](int r) { return reinterpret_cast<f32x4*>(out + (uint64_t)(uint32_t)r * (uint32_t)d * 4u); };
+  int at[kAhead][kPieces];
+  f32x4 old[kAhead][kPieces];
+  auto fetch = [&](int i) {
+#pragma unroll
+    for (int q = 0; q < kPieces; ++q) at[i % kAhead][q] = on ? row(i * 16 + q * 2 + hr) : -1;
+#pragma unroll
+    for (int q = 0; q < kPieces; ++q) {
+      f32x4 x = {0.f, 0.f, 0.f, 0.f};
+      if (add && at[i % kAhead][q] >= 0) x = *place(at[i % kAhead][q]);
+      old[i % kAhead][q] = x;
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i) fetch(i);
+#pragma unroll
+  for (int i = 0; i < kBlocksM; ++i) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < kBlocksN; ++j)
+#pragma unroll
+      for (int r = 0; r < kAccPerBlock; ++r) put[r * kLdsRowF + j * 16] = acc_get(acc, i, j, r);
+    __builtin_amdgcn_wave_barrier();   // (a wave's LDS accesses run in order)
+    f32x4 x[kPieces];
+#pragma unroll
+    for (int q = 0; q < kPieces; ++q)
+      x[q] = *reinterpret_cast<const f32x4*>(get + q * 2 * kLdsRowF) + old[i % kAhead][q];
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int q = 0; q < kPieces; ++q)
+      if (at[i % kAhead][q] >= 0) *place(at[i % kAhead][q]) = x[q];
+    if (i + kAhead < kBlocksM) fetch(i + kAhead);
+  }
+}
+
 // dW rows v0 + vl (A = Delta^T), columns = hidden features (B = H^T).
-// Addresses are a per-tile base plus 32-bit byte offsets (a tile spans
-// 384 rows of dW).  In accumulate mode each column block's 48 old values are
-// loaded, added and stored before the next block's loads (a compiler memory
-// fence between the blocks): hoisting every load of the tile would need 384
-// more registers.
 struct EpiDW {
   static constexpr bool kMaskRows = false;
   int V, d, v0;
   float* dW;
   bool accumulate;
 
-  __device__ __forceinline__ void apply(const AccTile& acc, int tm, int tn, int wm, int wn, int lane, float*) const {
-    const int row0 = v0 + tm * kTileM;                   // first dW row of the tile
-    const int lr = acc_row(wm, 0, 0, lane);              // this lane's tile rows: lr + i*16 + r
-    unsigned char* base = reinterpret_cast<unsigned char*>(dW + (int64_t)row0 * d + tn * kTileN);
-    const uint32_t ld = (uint32_t)d * 4;
-    const uint32_t loff = (uint32_t)lr * ld + (uint32_t)acc_col(wn, 0, lane) * 4;
-    const int cb = tn * kTileN + acc_col(wn, 0, lane);   // this lane's columns: cb + j*16
-#pragma unroll
-    for (int j = 0; j < kBlocksN; ++j) {
-      const bool cv = cb + j * 16 < d;
-      float old[kBlocksM][kAccPerBlock];
-#pragma unroll
-      for (int i = 0; i < kBlocksM; ++i)
-#pragma unroll
-        for (int r = 0; r < kAccPerBlock; ++r) {
-          const bool ok = accumulate && cv && row0 + lr + i * 16 + r < V;
-          const uint32_t off = loff + (uint32_t)(i * 16 + r) * ld + (uint32_t)j * 64;
-          old[i][r] = ok ? *reinterpret_cast<const float*>(base + off) : 0.f;
-        }
-#pragma unroll
-      for (int i = 0; i < kBlocksM; ++i)
-#pragma unroll
-        for (int r = 0; r < kAccPerBlock; ++r) {
-          const uint32_t off = loff + (uint32_t)(i * 16 + r) * ld + (uint32_t)j * 64;
-          if (cv && row0 + lr + i * 16 + r < V)
-            *reinterpret_cast<float*>(base + off) = old[i][r] + acc_get(acc, i, j, r);
-        }
-      asm volatile("" ::: "memory");
-    }
+  __device__ __forceinline__ void apply(const AccTile& acc, int tm, int tn, int wm, int wn, int, float* smem) const {
+    const int row0 = v0 + tm * kTileM + wm * kWaveM;   // of the wave
+    write_wave_rows(acc, wm * 2 + wn, smem, dW, d, tn * kTileN + wn * kWaveN, accumulate,
+                    [&](int r) { return row0 + r < V ? row0 + r : -1; });
   }
 };
 
 // dH rows = compacted tokens (A = Delta), columns = hidden features
-// (B = W^T[:, v0:]); row t is written to d_hidden row tok[t], t < *n_dev.
-// After the first vocabulary chunk each row block's old values are loaded,
-// added and stored before the next block's loads (see EpiDW).
+// (B = W^T[:, v0:]); row t is written to d_hidden row tok[t], t < *n_dev, and
+// added to it after the first vocabulary chunk.
 struct EpiDH {
   static constexpr bool kMaskRows = false;
   int N, d;
@@ -519,30 +548,11 @@ struct EpiDH {
   const int32_t* tok;
   const int32_t* n_dev;
 
-  __device__ __forceinline__ void apply(const AccTile& acc, int tm, int tn, int wm, int wn, int lane, float*) const {
+  __device__ __forceinline__ void apply(const AccTile& acc, int tm, int tn, int wm, int wn, int, float* smem) const {
+    const int row0 = tm * kTileM + wm * kWaveM;   // of the wave
     const int n = min(N, __builtin_amdgcn_readfirstlane(*n_dev));
-    const int cb = tn * kTileN + acc_col(wn, 0, lane);   // this lane's columns: cb + j*16
-#pragma unroll
-    for (int i = 0; i < kBlocksM; ++i) {
-      float* rows[kAccPerBlock];
-#pragma unroll
-      for (int r = 0; r < kAccPerBlock; ++r) {
-        const int t = tm * kTileM + acc_row(wm, i, r, lane);
-        rows[r] = t < n ? dH + (int64_t)tok[t] * d : nullptr;
-      }
-      float old[kAccPerBlock][kBlocksN];
-#pragma unroll
-      for (int r = 0; r < kAccPerBlock; ++r)
-#pragma unroll
-        for (int j = 0; j < kBlocksN; ++j)
-          old[r][j] = (!first && rows[r] != nullptr && cb + j * 16 < d) ? rows[r][cb + j * 16] : 0.f;
-#pragma unroll
-      for (int r = 0; r < kAccPerBlock; ++r)
-#pragma unroll
-        for (int j = 0; j < kBlocksN; ++j)
-          if (rows[r] != nullptr && cb + j * 16 < d) rows[r][cb + j * 16] = old[r][j] + acc_get(acc, i, j, r);
-      asm volatile("" ::: "memory");
-    }
+    write_wave_rows(acc, wm * 2 + wn, smem, dH, d, tn * kTileN + wn * kWaveN, !first,
+                    [&](int r) { return row0 + r < n ? tok[row0 + r] : -1; });
   }
 };
 
@@ -737,7 +747,9 @@ __global__ __launch_bounds__(kMergeThreads) void finalize_kernel(
   double cs = 0.0, acs = 0.0, nclip = 0.0, nzero = 0.0;
   float maxw = 0.f;
   if (t < N) {
-    const float lse = col >= 0 ? M + logf(L) : NAN;
+    // float64: rounded to float32, a log-prob of 12 is off by up to 5e-7, which the
+    // ratio and the signed sum of the loss then carry
+    const double lse = col >= 0 ? (double)M + log((double)L) : (double)NAN;
     const int tgt = target[t];
     const int seq = seq_id[t];
     const bool valid = tgt >= 0 && tgt < V && seq >= 0 && seq < R;
@@ -746,8 +758,9 @@ __global__ __launch_bounds__(kMergeThreads) void finalize_kernel(
     float l = NAN, s = 0.f, dl = 0.f;
     bool mu = false;
     if (valid && col >= 0) {
-      l = zt[col] - lse;
-      const float rho = expf(l - logp_old[t]);
+      const double l64 = (double)zt[col] - lse;
+      l = (float)l64;
+      const float rho = (float)exp(l64 - (double)logp_old[t]);
       const float clipped = fminf(fmaxf(rho, 1.f - eps_low), 1.f + eps_high);
       s = fminf(rho * A, clipped * A);
       mu = (A > 0.f && rho <= 1.f + eps_high) || (A < 0.f && rho >= 1.f - eps_low);
@@ -760,7 +773,7 @@ __global__ __launch_bounds__(kMergeThreads) void finalize_kernel(
       atomicOr(err_flag, (tgt >= 0 && tgt < V) ? PSPO_DEVERR_SEQ_ID : PSPO_DEVERR_TARGET);
     }
     // (a valid token without forward partials has A == 0: zero loss term and gradient)
-    lse_out[t] = lse;
+    lse_out[t] = (float)lse;
     delta_out[t] = dl;
     if (logp_new) logp_new[t] = l;
     cs = (double)c * (double)s;
@@ -819,10 +832,10 @@ __global__ __launch_bounds__(kFinThreads) void reduce_loss_kernel(int nblk, cons
 // (gemm_nt_kernel with kLaunchRounds, then kLaunchTail + EpiSlab): each tail
 // tile's K parts are summed in order from the slabs of its work-groups
 // x + 8 (u S + p) and handed to `out` row by row, 16 values at a time.
-// Grid (24 blocks of 16 rows, 8 XCDs x 32 tail tiles), 256 threads.
+// Grid (24 blocks of 16 rows, 8 XCDs x the tail tiles an XCD can have), 256 threads.
 template <class Out>
 __global__ __launch_bounds__(256) void tail_reduce_kernel(GemmShape g, const float* __restrict__ slab, Out out) {
-  __shared__ float rows[16][kTileN + 4];
+  __shared__ __attribute__((aligned(16))) float rows[16][kTileN + 4];
   int M, N, K;
   bounded_dims(g, M, N, K);
   const TileGrid tg = tile_grid(g.tiles_m, g.tiles_n, M, N);
@@ -839,6 +852,8 @@ __global__ __launch_bounds__(256) void tail_reduce_kernel(GemmShape g, const flo
   f32x4 sum[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) sum[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // (up to 64 parts, in order; one at a time their loads' latency took 47 us)
+#pragma unroll 8
   for (int p = 0; p < parts; ++p) {
     const f32x4* src = reinterpret_cast<const f32x4*>(slab + (int64_t)(x + kNumXcd * (u * parts + p)) * (kTileM * kTileN) +
                                                       rb * (16 * kTileN) + tid * 16);
@@ -861,10 +876,10 @@ struct TailDW {
   bool accumulate;
   __device__ __forceinline__ void operator()(int row, int col0, const float* v) const {
     if (v0 + row >= V) return;
-    float* o = dW + (int64_t)(v0 + row) * d;
+    f32x4* o = reinterpret_cast<f32x4*>(dW + (int64_t)(v0 + row) * d + col0);
 #pragma unroll
-    for (int e = 0; e < 16; ++e)
-      if (col0 + e < d) o[col0 + e] = (accumulate ? o[col0 + e] : 0.f) + v[e];
+    for (int e = 0; e < 4; ++e)
+      if (col0 + 4 * e < d) o[e] = (accumulate ? o[e] : f32x4{0.f, 0.f, 0.f, 0.f}) + reinterpret_cast<const f32x4*>(v)[e];
   }
 };
 
@@ -877,10 +892,10 @@ struct TailDH {
   const int32_t* n_dev;
   __device__ __forceinline__ void operator()(int row, int col0, const float* v) const {
     if (row >= min(N, *n_dev)) return;
-    float* o = dH + (int64_t)tok[row] * d;
+    f32x4* o = reinterpret_cast<f32x4*>(dH + (int64_t)tok[row] * d + col0);
 #pragma unroll
-    for (int e = 0; e < 16; ++e)
-      if (col0 + e < d) o[col0 + e] = (first ? 0.f : o[col0 + e]) + v[e];
+    for (int e = 0; e < 4; ++e)
+      if (col0 + 4 * e < d) o[e] = (first ? f32x4{0.f, 0.f, 0.f, 0.f} : o[e]) + reinterpret_cast<const f32x4*>(v)[e];
   }
 };
 
@@ -1254,7 +1269,12 @@ int launch_gemm(const GemmShape& g, const Epi& epi, hipStream_t stream) {
 
 // A product with long tiles as whole rounds (epilogue `epi`), then the
 // remaining tiles split along K into slabs, then their sums (written by `out`
-// as `epi` would write them): the CUs stay busy through the last round.
+// as `epi` would write them): the CUs stay busy through the last round.  The
+// slabs of a tail (up to 201 MB) are written and read back and cost two more
+// launches, about as much as 256 K steps of a partial round take: a product
+// whose K can only be shorter is launched whole (dW of fewer than 8,192 tokens;
+// at 2,048 tokens the split tails and their sums took 700 us of 8.5 ms).
+constexpr int kSplitSteps = 256;
 template <class Epi, class Out>
 int launch_gemm_split_tail(const GemmShape& g, const Epi& epi, const Out& out, float* slab, hipStream_t stream) {
   hipLaunchKernelGGL((gemm_nt_kernel<Epi, kLaunchRounds>), dim3(gemm_grid(g.tiles_m, g.tiles_n)), dim3(kGemmThreads),
@@ -1263,7 +1283,8 @@ int launch_gemm_split_tail(const GemmShape& g, const Epi& epi, const Out& out, f
   hipLaunchKernelGGL((gemm_nt_kernel<EpiSlab, kLaunchTail>), dim3(kNumXcd * kTailSlots), dim3(kGemmThreads), 0,
                      stream, g, EpiSlab{slab});
   PSPO_LAUNCHED("gemm_nt_kernel (K-split tail)", stream);
-  hipLaunchKernelGGL(tail_reduce_kernel<Out>, dim3(kTileM / 16, kNumXcd * 32), dim3(256), 0, stream, g,
+  const int most = std::min((g.tiles_m * g.tiles_n + kNumXcd - 1) / kNumXcd, 31);   // of per_xcd % 32
+  hipLaunchKernelGGL(tail_reduce_kernel<Out>, dim3(kTileM / 16, (unsigned)(kNumXcd * most)), dim3(256), 0, stream, g,
                      (const float*)slab, out);
   PSPO_LAUNCHED("tail_reduce_kernel", stream);
   return PSPO_OK;
@@ -1449,8 +1470,11 @@ int pspo_loss_fwd_bwd(const uint16_t* hidden, const uint16_t* w_head, const int3
                   kTileM, pl.Npad * kTileM * 2};
       EpiDW e{V, d, (int)v0, d_w_head, accumulate};
       if (int rc = t_dw.begin(PSPO_TIME_DW)) return rc;
-      if (int rc = launch_gemm_split_tail(g, e, TailDW{V, d, (int)v0, d_w_head, accumulate}, slab, stream))
+      if (pl.Npad / kTileK < kSplitSteps) {
+        if (int rc = launch_gemm(g, e, stream)) return rc;
+      } else if (int rc = launch_gemm_split_tail(g, e, TailDW{V, d, (int)v0, d_w_head, accumulate}, slab, stream)) {
         return rc;
+      }
       if (int rc = t_dw.end()) return rc;
     }
     {
