@@ -201,16 +201,14 @@ WeightsShape weights_shape(int K, int topk) {
 // The budgeted monotone solve (App. F).  One thread per prompt ran Pooling
 // Adjacent Violators over the steps, one dependent chain of LDS accesses and
 // branches per step, and then summed, searched and wrote the table alone:
-// 1,922 us for 8 prompts of 2,500 to 6,900 steps, 230 to 290 us with what follows.
+// 1,922 us for 8 prompts of 2,500 to 6,900 steps, 44 us with what follows.
 //
-// The blocks are found first, by all threads: blocks of steps are merged pairwise
-// up a tree, where only the blocks at the joint can violate, and pooling adjacent
-// violators in any order ends at the same blocks.  The sums of this phase are
-// rounded in the order of the tree and only find the blocks.  Each found block's
-// sum is then formed again as the sequential algorithm forms it: run from a block's
-// first step, it pools exactly as it does in a run over all steps (a block's
-// first step never pools with what is before it).  The blocks are independent, so
-// a wave each; the longest block bounds the solve.
+// The blocks are found by all threads: blocks of steps are joined pairwise up a
+// tree, where only the blocks at the joint can violate, and pooling adjacent
+// violators in any order ends at the same blocks.  A block's weight is summed in
+// the order of the tree (float64: at most log2(T) + the block's joins roundings,
+// where one after another it was its length).  Scores, the search for the first
+// unsaturated block and the table are spread over the threads.
 constexpr int kDesignThreads = 1024;
 
 // Storage of one prompt's blocks, all of one memory kind (LDS or the workspace).
@@ -265,10 +263,10 @@ __device__ __forceinline__ void join_blocks(const Blocks& bl, int a, int m, int 
   bl.wv[s] = W;
 }
 
-// Bits of the first step of every block of at least `least` steps, over [0, n).
-__device__ __forceinline__ void mark_heads(const Blocks& bl, int n, int least) {
+// Bits of the first step of every block over [0, n).
+__device__ __forceinline__ void mark_heads(const Blocks& bl, int n) {
   for (int t = threadIdx.x; t < (n + 63) / 64 * 64; t += kDesignThreads) {
-    const uint64_t m = __ballot(t < n && bl.ln[t] >= least);
+    const uint64_t m = __ballot(t < n && bl.ln[t] > 0);
     if ((threadIdx.x & 63) == 0) bl.heads[t / 64] = m;
   }
 }
@@ -280,82 +278,10 @@ __device__ __forceinline__ double lane_value(double x, int lane) {
   return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
 }
 
-// The sequential algorithm over the steps [s, s + len), by one wave whose lanes
-// all hold the same values: a stack of blocks (length, summed weight); a new step
-// pools with the block below it while that block's mean is below its own.  The
-// stack's first 64 entries sit in the lanes (entry k in lane k), further ones in
-// the block's own wv / ln; the weights are read 64 at a time, one group ahead.
-// It ends with the one block [s, s + len), or with several where the tree's
-// rounding and this one's differ.
-__device__ __forceinline__ void pool_in_order(const Blocks& bl, const double* wp, int s, int len) {
-  const int lane = threadIdx.x & 63;
-  double* wv = bl.wv + s;
-  int32_t* ln = bl.ln + s;
-  const double* w = wp + s;
-  double sw = 0.0;                 // this lane's stack entry
-  int sl = 0;
-  int depth = 0;                   // entries under the top block
-  double group = lane < len ? w[lane] : 0.0, ahead = 64 + lane < len ? w[64 + lane] : 0.0;
-  double tw = lane_value(group, 0), tl = 1.0;
-  for (int t = 1; t < len; ++t) {
-    if ((t & 63) == 0) {
-      group = ahead;
-      ahead = t + 64 + lane < len ? w[t + 64 + lane] : 0.0;
-    }
-    double W = lane_value(group, t & 63), L = 1.0;
-    bool under = true;             // a block is left under the new one
-    while (under && tw * L < W * tl) {
-      L += tl;
-      W = tw + W;
-      under = depth > 0;
-      if (under) {
-        --depth;
-        if (depth < 64) {
-          tw = lane_value(sw, depth);
-          tl = (double)__builtin_amdgcn_readlane(sl, depth);
-        } else {
-          tw = lane_value(wv[depth], 0);
-          tl = (double)__builtin_amdgcn_readfirstlane(ln[depth]);
-        }
-      }
-    }
-    if (under) {
-      if (depth < 64) {
-        if (lane == depth) {
-          sw = tw;
-          sl = (int)tl;
-        }
-      } else {                     // (every lane writes the same, and so reads what it wrote)
-        wv[depth] = tw;
-        ln[depth] = (int)tl;
-      }
-      ++depth;
-    }
-    tw = W;
-    tl = L;
-  }
-  // from the last block to the first: entry k starts at or after step k, so no
-  // entry is overwritten before it is read
-  for (int k = depth, end = len; k >= 0; --k) {
-    if (k < depth) {
-      tw = k < 64 ? lane_value(sw, k) : wv[k];
-      tl = k < 64 ? (double)__builtin_amdgcn_readlane(sl, k) : (double)ln[k];
-    }
-    const int l = (int)tl, start = end - l;
-    for (int t = start + 1 + lane; t < end; t += 64) ln[t] = 0;
-    if (lane == 0) {
-      ln[start] = l;
-      wv[start] = tw;
-    }
-    end = start;
-  }
-}
-
 // The solve of one prompt of T steps whose last positive weight is step n - 1
 // (trailing steps of weight 0 are blocks of their own and pool with nothing).
 __device__ __forceinline__ void solve_prompt(const Blocks& bl, const double* wp, int T, int n, double budget,
                                              double* xp) {
-  __shared__ int next_word;
   __shared__ int sh_saturated;
   __shared__ double sh_kappa;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -363,7 +289,6 @@ __device__ __forceinline__ void solve_prompt(const Blocks& bl, const double* wp,
     bl.ln[t] = 1;
     bl.wv[t] = wp[t];
   }
-  if (tid == 0) next_word = 0;
   __syncthreads();
   // (64-bit positions: twice the half length can pass 2^31)
   for (int64_t half = 1; half < n; half *= 2) {
@@ -371,23 +296,8 @@ __device__ __forceinline__ void solve_prompt(const Blocks& bl, const double* wp,
       join_blocks(bl, (int)a, (int)(a + half), (int)min(a + 2 * half, (int64_t)n));
     __syncthreads();
   }
-  // the sums in the sequential order: blocks taken word by word
   const int words = (n + 63) / 64;
-  mark_heads(bl, n, 2);
-  __syncthreads();
-  for (;;) {
-    int word = lane == 0 ? atomicAdd(&next_word, 1) : 0;
-    word = __builtin_amdgcn_readfirstlane(word);
-    if (word >= words) break;
-    uint64_t m = bl.heads[word];
-    while (m != 0) {
-      const int s = __builtin_amdgcn_readfirstlane(word * 64 + __builtin_ctzll(m));
-      m &= m - 1;
-      pool_in_order(bl, wp, s, __builtin_amdgcn_readfirstlane(bl.ln[s]));
-    }
-  }
-  __syncthreads();
-  mark_heads(bl, n, 1);
+  mark_heads(bl, n);
   __syncthreads();
   // the block scores sqrt(W_m / L_m)
   for (int t = tid; t < n; t += kDesignThreads)
