@@ -167,10 +167,16 @@ __global__ void pack_fill_kernel(const int32_t* __restrict__ cu_seqlens, const i
   }
 }
 
-// Copies the kept hidden rows, one wave per row, 16 bytes per lane.
-__global__ void pack_hidden_kernel(const int32_t* __restrict__ cu_seqlens, const int32_t* __restrict__ full_off,
-                                   int32_t capacity, const u32x4* __restrict__ hidden_full,
-                                   u32x4* __restrict__ hidden, int32_t vec_per_row) {
+// Copies the kept hidden rows: one wave per row, 16 bytes per lane, kPieces loads
+// in flight before their stores; the copy is read by later kernels from memory, so
+// both go past the caches.  One load at a time and its store, through the caches:
+// 688 us for the sampling and packing of 32 completions of up to 16,384 tokens,
+// d = 3584 (2.8 GB moved); now 625 us, 4.5 TB/s.
+__global__ __launch_bounds__(256) void pack_hidden_kernel(const int32_t* __restrict__ cu_seqlens,
+                                                          const int32_t* __restrict__ full_off, int32_t capacity,
+                                                          const u32x4* __restrict__ hidden_full,
+                                                          u32x4* __restrict__ hidden, int32_t vec_per_row) {
+  constexpr int kPieces = 8;
   const int r = blockIdx.y;
   const int32_t c0 = cu_seqlens[r], H = cu_seqlens[r + 1] - c0;
   const int32_t f0 = full_off[r];
@@ -181,7 +187,15 @@ __global__ void pack_hidden_kernel(const int32_t* __restrict__ cu_seqlens, const
     if (i >= capacity) break;
     const u32x4* src = hidden_full + (int64_t)(f0 + j) * vec_per_row;
     u32x4* dst = hidden + i * vec_per_row;
-    for (int c = lane; c < vec_per_row; c += 64) dst[c] = src[c];
+    for (int b = lane; b < vec_per_row; b += 64 * kPieces) {
+      u32x4 x[kPieces];
+#pragma unroll
+      for (int q = 0; q < kPieces; ++q)
+        if (b + 64 * q < vec_per_row) x[q] = __builtin_nontemporal_load(src + b + 64 * q);
+#pragma unroll
+      for (int q = 0; q < kPieces; ++q)
+        if (b + 64 * q < vec_per_row) __builtin_nontemporal_store(x[q], dst + b + 64 * q);
+    }
   }
 }
 
