@@ -1,5 +1,5 @@
 """GPU: the float32 target entries of dW, against the float64 oracle, where their summation can go
-wrong: column counts around a span (32) and a sorted block (8192), ids whose columns fill many spans
+wrong: column counts around a span (32) and a sorted block (2048), ids whose columns fill many spans
 (one id for every token; a 1/rank law, as real token ids follow), end on a span's edge or hold one
 column each, and widths around a wave's 256- and 512-feature slices.
 
@@ -21,8 +21,8 @@ from parity_util import f32
 pytestmark = pytest.mark.gpu
 
 CASES = [(1, 24, "one"), (31, 24, "one"), (32, 24, "one"), (33, 24, "one"), (64, 8, "pairs"), (65, 1032, "ranked"),
-         (97, 24, "distinct"), (640, 264, "spans"), (2050, 520, "ranked"), (8191, 24, "one"), (8192, 24, "ranked"),
-         (8193, 24, "ranked"), (16500, 24, "one"), (16500, 256, "ranked")]
+         (97, 24, "distinct"), (640, 264, "spans"), (2050, 520, "ranked"), (2047, 24, "ranked"), (2048, 24, "one"), (2049, 24, "ranked"),
+         (8191, 24, "one"), (8192, 24, "ranked"), (8193, 24, "ranked"), (16500, 24, "one"), (16500, 256, "ranked")]
 
 
 def _targets(rng, N, V, law):
