@@ -70,6 +70,8 @@
 // (shared through the memory-side cache).
 #pragma once
 
+#include <cmath>
+
 #include "common.h"
 
 namespace pspo {
@@ -288,19 +290,31 @@ __device__ __forceinline__ bool map_tile(int tiles_m, int tiles_n, int M, int N,
   return map_tile_at(blockIdx.x, tiles_m, tiles_n, M, N, tm, tn, spread_m, rounds_only);
 }
 
-// K parts of each tail tile of an XCD with r tail tiles and nk K steps: the
-// S <= min(64 / r, nk) with the fewest rounds per part, ceil(r S / 32) / S
-// (the smaller S on ties).
+// K parts of each tail tile of an XCD with r (1 .. 31) tail tiles and nk K steps:
+// the S <= min(64 / r, nk) of the least time, estimated in twentieths of a
+// microsecond as ceil(r S / 32) rounds of nk / S K steps (0.85 us each) and the
+// slabs of 8 r S parts written and read back (393 KB each at about 4.5 TB/s:
+// 1.4 us per r S).  At a given number of rounds (one or two) that is a nk / S +
+// b S, least at S = sqrt(a nk / b).  (Every work-group of a tail computes this: a
+// search over all S, with its divisions, takes some 10 us there.)
+__host__ __device__ inline int tail_cost(int r, int nk, int s) {
+  return (r * s > 32 ? 2 : 1) * ((nk + s - 1) / s) * 17 + r * s * 28;
+}
 __host__ __device__ inline int tail_parts(int r, int nk) {
-  int best = 1, best_rounds = (r + 31) / 32;
-  for (int s = 2; s * r <= kTailSlots && s <= nk; ++s) {
-    const int rounds = (r * s + 31) / 32;
-    if (rounds * best < best_rounds * s) {
-      best = s;
-      best_rounds = rounds;
-    }
-  }
-  return best;
+  const float best1 = sqrtf((float)nk * 17.f / (float)(28 * r));
+  const int one = max(min(min(kTailSlots / 2 / r, nk), (int)best1), 1);
+  const int two = max(min(min(kTailSlots / r, nk), (int)(1.4142f * best1)), 1);
+  return tail_cost(r, nk, two) < tail_cost(r, nk, one) ? two : one;
+}
+
+// Whether a launch of tiles_m x tiles_n tiles of nk K steps is better split: its
+// last round in parts (plus two launches, 25 us) against a whole tile's time and
+// epilogue (30 us).  A dW product of 200 tokens is launched whole (2,418 against
+// 2,465 us a call), one of 5,000 split (1,811 against 1,999 us on V = 50021).
+inline bool split_tail_pays(int tiles_m, int tiles_n, int nk) {
+  const int64_t per_xcd = ((int64_t)tiles_m * tiles_n + kNumXcd - 1) / kNumXcd;
+  const int r = (int)(per_xcd % 32);
+  return r > 0 && tail_cost(r, nk, tail_parts(r, nk)) + 500 < 17 * nk + 600;
 }
 
 // Epilogue of a tail launch: the part's accumulators to slab `blockIdx.x`.
@@ -312,24 +326,25 @@ struct EpiSlab {
   }
 };
 
-// Tail launch: work-group x + 8 k (x the XCD, k < 64) takes part k % S of the
-// XCD's tail tile k / S, K steps [part nk / S, (part + 1) nk / S).  The tail
-// tiles are the positions after the XCD's whole rounds.  Returns false for
-// work-groups without a part.
-__host__ __device__ inline bool map_tail(const TileGrid& tg, int bid, int nk, int& tm, int& tn, int& kb, int& ke,
-                                         int* u_out = nullptr, int* parts_out = nullptr) {
+// Tail launch: work-group x + 8 k (x the XCD, k < 64) takes part k / r of the
+// XCD's tail tile k % r, K steps [part nk / S, (part + 1) nk / S).  The tail
+// tiles are the positions after the XCD's whole rounds.  The tiles of one part lie
+// next to each other, so that an XCD's L2 serves the panels they share: the
+// neighbours in the grouped order are up to 4 row tiles of a column tile, and with
+// the parts of a tile next to each other instead each of the 32 running
+// work-groups read its own row panel (2,048 tokens: 7,317 -> 7,198 us a call).  Returns false for work-groups
+// without a part.
+__host__ __device__ inline bool map_tail(const TileGrid& tg, int bid, int nk, int& tm, int& tn, int& kb, int& ke) {
   const int x = bid % kNumXcd, k = bid / kNumXcd;
   const int full = tg.per_xcd / 32 * 32;
   const int r = xcd_count(tg, x) - full;
   if (r <= 0 || k >= kTailSlots) return false;
   const int parts = tail_parts(r, nk);
-  const int u = k / parts, part = k % parts;
-  if (u >= r) return false;
+  const int u = k % r, part = k / r;
+  if (part >= parts) return false;
   tile_at(tg, xcd_position(tg, x, full + u), 0, tm, tn);
   kb = part * nk / parts;
   ke = (part + 1) * nk / parts;
-  if (u_out) *u_out = u;
-  if (parts_out) *parts_out = parts;
   return true;
 }
 

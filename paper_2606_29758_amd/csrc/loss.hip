@@ -471,7 +471,7 @@ __global__ __launch_bounds__(256) void zero_targets_kernel(int N, const int32_t*
 // as far as they exist (d % 8 == 0).  Straight from
 // the accumulators a store moved 4 bytes per lane in 64-byte pieces of four rows,
 // and adding waited for a batch of such loads before each batch of stores.  With the dW product launched whole
-// where its K is short (launch_gemm_split_tail): 200 tokens on the 7B-shaped head
+// where its K is short (split_tail_pays): 200 tokens on the 7B-shaped head
 // (2.2 GB of dW written) 3,366 -> 2,450 us a call, 2,048 tokens that add to dW
 // 8,510 -> 7,391 us.
 template <class Row>
@@ -831,10 +831,14 @@ __global__ __launch_bounds__(kFinThreads) void reduce_loss_kernel(int nblk, cons
 // The tail tiles of a product launched as whole rounds plus a K-split tail
 // (gemm_nt_kernel with kLaunchRounds, then kLaunchTail + EpiSlab): each tail
 // tile's K parts are summed in order from the slabs of its work-groups
-// x + 8 (u S + p) and handed to `out` row by row, 16 values at a time.
-// Grid (24 blocks of 16 rows, 8 XCDs x the tail tiles an XCD can have), 256 threads.
+// x + 8 (p r + u) and handed to `out` four columns of a row at a time.  A thread
+// sums one 16-byte piece, with up to kPartsAhead parts in flight: with a quarter
+// of the threads and a part at a time the latency of 32 parts took 43 us.
+// Grid (24 blocks of 16 rows, 8 XCDs x the tail tiles an XCD can have).
+constexpr int kTailThreads = 1024, kPartsAhead = 8;
 template <class Out>
-__global__ __launch_bounds__(256) void tail_reduce_kernel(GemmShape g, const float* __restrict__ slab, Out out) {
+__global__ __launch_bounds__(kTailThreads) void tail_reduce_kernel(GemmShape g, const float* __restrict__ slab,
+                                                                   Out out) {
   __shared__ __attribute__((aligned(16))) float rows[16][kTileN + 4];
   int M, N, K;
   bounded_dims(g, M, N, K);
@@ -847,26 +851,26 @@ __global__ __launch_bounds__(256) void tail_reduce_kernel(GemmShape g, const flo
   int tm, tn;
   tile_at(tg, xcd_position(tg, x, full + u), 0, tm, tn);
   const int rb = blockIdx.x, tid = threadIdx.x;
-  // the slab layout [24 blocks of 16 rows][256 columns][16]: column tid of row
-  // block rb is 16 consecutive floats
-  f32x4 sum[4];
+  // the slab layout [24 blocks of 16 rows][256 columns][16]: thread tid takes
+  // rows 4 (tid % 4) .. +3 of column tid / 4 of row block rb
+  constexpr int64_t kSlabPieces = kTileM * kTileN / 4;
+  const f32x4* src = reinterpret_cast<const f32x4*>(slab) + (x + kNumXcd * u) * kSlabPieces +
+                     rb * (4 * kTileN) + tid;
+  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+  for (int p = 0; p < parts; p += kPartsAhead) {
+    f32x4 part[kPartsAhead];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) sum[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // (up to 64 parts, in order; one at a time their loads' latency took 47 us)
-#pragma unroll 8
-  for (int p = 0; p < parts; ++p) {
-    const f32x4* src = reinterpret_cast<const f32x4*>(slab + (int64_t)(x + kNumXcd * (u * parts + p)) * (kTileM * kTileN) +
-                                                      rb * (16 * kTileN) + tid * 16);
+    for (int e = 0; e < kPartsAhead; ++e)   // (past the last part: it once more, not added)
+      part[e] = __builtin_nontemporal_load(src + (int64_t)min(p + e, parts - 1) * r * (kNumXcd * kSlabPieces));
 #pragma unroll
-    for (int q = 0; q < 4; ++q) sum[q] += __builtin_nontemporal_load(src + q);
+    for (int e = 0; e < kPartsAhead; ++e)
+      if (p + e < parts) sum += part[e];
   }
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) rows[q * 4 + e][tid] = sum[q][e];
+  for (int e = 0; e < 4; ++e) rows[(tid & 3) * 4 + e][tid >> 2] = sum[e];
   __syncthreads();
-  const int lr = tid >> 4, c0 = (tid & 15) * 16;
-  out(tm * kTileM + rb * 16 + lr, tn * kTileN + c0, &rows[lr][c0]);
+  const int lr = tid >> 6, c0 = (tid & 63) * 4;
+  out(tm * kTileM + rb * 16 + lr, tn * kTileN + c0, *reinterpret_cast<const f32x4*>(&rows[lr][c0]));
 }
 
 // dW rows v0 + row (< V), as EpiDW writes them: (accumulate ? old : 0) + sum.
@@ -874,12 +878,10 @@ struct TailDW {
   int V, d, v0;
   float* dW;
   bool accumulate;
-  __device__ __forceinline__ void operator()(int row, int col0, const float* v) const {
-    if (v0 + row >= V) return;
+  __device__ __forceinline__ void operator()(int row, int col0, const f32x4& v) const {
+    if (v0 + row >= V || col0 >= d) return;
     f32x4* o = reinterpret_cast<f32x4*>(dW + (int64_t)(v0 + row) * d + col0);
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (col0 + 4 * e < d) o[e] = (accumulate ? o[e] : f32x4{0.f, 0.f, 0.f, 0.f}) + reinterpret_cast<const f32x4*>(v)[e];
+    *o = accumulate ? *o + v : v;
   }
 };
 
@@ -890,12 +892,10 @@ struct TailDH {
   bool first;
   const int32_t* tok;
   const int32_t* n_dev;
-  __device__ __forceinline__ void operator()(int row, int col0, const float* v) const {
-    if (row >= min(N, *n_dev)) return;
+  __device__ __forceinline__ void operator()(int row, int col0, const f32x4& v) const {
+    if (row >= min(N, *n_dev) || col0 >= d) return;
     f32x4* o = reinterpret_cast<f32x4*>(dH + (int64_t)tok[row] * d + col0);
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (col0 + 4 * e < d) o[e] = (first ? f32x4{0.f, 0.f, 0.f, 0.f} : o[e]) + reinterpret_cast<const f32x4*>(v)[e];
+    *o = first ? v : *o + v;
   }
 };
 
@@ -1271,12 +1271,7 @@ int launch_gemm(const GemmShape& g, const Epi& epi, hipStream_t stream) {
 
 // A product with long tiles as whole rounds (epilogue `epi`), then the
 // remaining tiles split along K into slabs, then their sums (written by `out`
-// as `epi` would write them): the CUs stay busy through the last round.  The
-// slabs of a tail (up to 201 MB) are written and read back and cost two more
-// launches, about as much as 256 K steps of a partial round take: a product
-// whose K can only be shorter is launched whole (dW of fewer than 8,192 tokens;
-// at 2,048 tokens the split tails and their sums took 700 us of 8.5 ms).
-constexpr int kSplitSteps = 256;
+// as `epi` would write them): the CUs stay busy through the last round.
 template <class Epi, class Out>
 int launch_gemm_split_tail(const GemmShape& g, const Epi& epi, const Out& out, float* slab, hipStream_t stream) {
   hipLaunchKernelGGL((gemm_nt_kernel<Epi, kLaunchRounds>), dim3(gemm_grid(g.tiles_m, g.tiles_n)), dim3(kGemmThreads),
@@ -1286,7 +1281,7 @@ int launch_gemm_split_tail(const GemmShape& g, const Epi& epi, const Out& out, f
                      stream, g, EpiSlab{slab});
   PSPO_LAUNCHED("gemm_nt_kernel (K-split tail)", stream);
   const int most = std::min((g.tiles_m * g.tiles_n + kNumXcd - 1) / kNumXcd, 31);   // of per_xcd % 32
-  hipLaunchKernelGGL(tail_reduce_kernel<Out>, dim3(kTileM / 16, (unsigned)(kNumXcd * most)), dim3(256), 0, stream, g,
+  hipLaunchKernelGGL(tail_reduce_kernel<Out>, dim3(kTileM / 16, (unsigned)(kNumXcd * most)), dim3(kTailThreads), 0, stream, g,
                      (const float*)slab, out);
   PSPO_LAUNCHED("tail_reduce_kernel", stream);
   return PSPO_OK;
@@ -1472,7 +1467,8 @@ int pspo_loss_fwd_bwd(const uint16_t* hidden, const uint16_t* w_head, const int3
                   kTileM, pl.Npad * kTileM * 2};
       EpiDW e{V, d, (int)v0, d_w_head, accumulate};
       if (int rc = t_dw.begin(PSPO_TIME_DW)) return rc;
-      if (pl.Npad / kTileK < kSplitSteps) {
+      // (K is the backward tokens: about two thirds of them)
+      if (!split_tail_pays(ctiles, tiles_d, (int)((int64_t)N * 2 / 3 / kTileK))) {
         if (int rc = launch_gemm(g, e, stream)) return rc;
       } else if (int rc = launch_gemm_split_tail(g, e, TailDW{V, d, (int)v0, d_w_head, accumulate}, slab, stream)) {
         return rc;
