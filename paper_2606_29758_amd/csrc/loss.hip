@@ -570,11 +570,12 @@ constexpr int kCompactThreads = 256, kCompactPer = 8, kCompactSpan = kCompactThr
 
 // Order-preserving compaction of the tokens t < N with keep(t) in two
 // launches over blocks of kCompactSpan consecutive tokens: the first counts
-// each block's kept tokens; the second adds the counts of the blocks before
-// it and scatters: idx[0 .. count) are the kept indices in increasing order,
-// pos[t] (if pos is not NULL) is t's place in idx or -1, mapped[p] (if mapped
-// is not NULL) is map[idx[p]]; the last block writes the count (and stats[4],
-// if asked).
+// each block's kept tokens (left out when there is one block); the second adds
+// the counts of the blocks before it and scatters: idx[0 .. count) are the kept
+// indices in increasing order, pos[t] (if pos is not NULL) is t's place in idx or
+// -1, emit.store(p, emit.load(t)) writes what else belongs to place p (a thread's
+// loads all go out before its stores); the last block writes the count (and
+// stats[4], if asked).
 template <class Keep>
 __global__ __launch_bounds__(kCompactThreads) void compact_count_kernel(int N, Keep keep, int32_t* __restrict__ cnt) {
   __shared__ int sh[kCompactThreads];
@@ -594,13 +595,11 @@ __global__ __launch_bounds__(kCompactThreads) void compact_count_kernel(int N, K
   if (threadIdx.x == 0) cnt[blockIdx.x] = sh[0];
 }
 
-template <class Keep>
-__global__ __launch_bounds__(kCompactThreads) void compact_scatter_kernel(int N, Keep keep,
+template <class Keep, class Emit>
+__global__ __launch_bounds__(kCompactThreads) void compact_scatter_kernel(int N, Keep keep, Emit emit,
                                                                           const int32_t* __restrict__ cnt,
                                                                           int32_t* __restrict__ idx,
                                                                           int32_t* __restrict__ pos,
-                                                                          const int32_t* __restrict__ map,
-                                                                          int32_t* __restrict__ mapped,
                                                                           int32_t* __restrict__ count,
                                                                           double* __restrict__ stats) {
   __shared__ int sh[kCompactThreads];
@@ -634,13 +633,17 @@ __global__ __launch_bounds__(kCompactThreads) void compact_scatter_kernel(int N,
     __syncthreads();
   }
   int p = o + sh[threadIdx.x] - c;
+  typename Emit::Row row[kCompactPer];
+#pragma unroll
+  for (int e = 0; e < kCompactPer; ++e)
+    if (kept[e]) row[e] = emit.load(t0 + e);
 #pragma unroll
   for (int e = 0; e < kCompactPer; ++e) {
     const int t = t0 + e;
     if (t < N) {
       if (kept[e]) {
         idx[p] = t;
-        if (mapped) mapped[p] = map[t];
+        emit.store(p, row[e]);
       }
       if (pos) pos[t] = kept[e] ? p : -1;
     }
@@ -675,14 +678,59 @@ struct KeepActive {
   __device__ bool operator()(int t) const { return delta[t] != 0.f; }
 };
 
-template <class Keep>
-int launch_compact(int N, const Keep& keep, int32_t* cnt, int32_t* idx, int32_t* pos, const int32_t* map,
-                   int32_t* mapped, int32_t* count, double* stats, hipStream_t stream) {
+// The target of each forward column.
+struct EmitForward {
+  typedef int32_t Row;
+  const int32_t* target;
+  int32_t* ftgt;
+  __device__ Row load(int t) const { return target[t]; }
+  __device__ void store(int p, Row row) const { ftgt[p] = row; }
+};
+
+// Per backward column a (token t): its forward column (where the kept logits
+// sit), target, lse and delta, in column order, so the backward kernels fetch a
+// column's data in one contiguous round trip; and the target entry of its
+// logit-gradient row, G_{o} = delta (1 - p(o)), as -delta expm1(l) with
+// l = z_o - lse the token's log-prob (no cancellation as p(o) -> 1).  A backward
+// token has delta != 0, hence a forward column.
+struct EmitBackward {
+  struct Row {
+    int f, tgt;
+    float lse, delta, z;
+  };
+  const int32_t* fpos;
+  const int32_t* target;
+  const float* lse;
+  const float* delta;
+  const float* zt;
+  int32_t* afwd;
+  int32_t* ctgt;
+  float* clse;
+  float* cdelta;
+  float* cg1;
+  __device__ Row load(int t) const {
+    const int f = fpos[t];
+    return Row{f, target[t], lse[t], delta[t], zt[f]};
+  }
+  __device__ void store(int a, const Row& row) const {
+    afwd[a] = row.f;
+    ctgt[a] = row.tgt;
+    clse[a] = row.lse;
+    cdelta[a] = row.delta;
+    cg1[a] = -row.delta * expm1f(row.z - row.lse);
+  }
+};
+
+template <class Keep, class Emit>
+int launch_compact(int N, const Keep& keep, const Emit& emit, int32_t* cnt, int32_t* idx, int32_t* pos, int32_t* count,
+                   double* stats, hipStream_t stream) {
   const unsigned nblk = (unsigned)((N + kCompactSpan - 1) / kCompactSpan);
-  hipLaunchKernelGGL(compact_count_kernel<Keep>, dim3(nblk), dim3(kCompactThreads), 0, stream, N, keep, cnt);
-  PSPO_LAUNCHED("compact_count_kernel", stream);
-  hipLaunchKernelGGL(compact_scatter_kernel<Keep>, dim3(nblk), dim3(kCompactThreads), 0, stream, N, keep, cnt, idx,
-                     pos, map, mapped, count, stats);
+  if (nblk > 1) {
+    hipLaunchKernelGGL(compact_count_kernel<Keep>, dim3(nblk), dim3(kCompactThreads), 0, stream, N, keep, cnt);
+    PSPO_LAUNCHED("compact_count_kernel", stream);
+  }
+  hipLaunchKernelGGL((compact_scatter_kernel<Keep, Emit>), dim3(nblk), dim3(kCompactThreads), 0, stream, N, keep, emit,
+                     cnt, idx, pos, count, stats);
   PSPO_LAUNCHED("compact_scatter_kernel", stream);
   return PSPO_OK;
 }
@@ -898,34 +946,6 @@ struct TailDH {
     *o = first ? v : *o + v;
   }
 };
-
-// Per backward column a < min(N, *n_dev) (token act[a]): its forward column
-// (where the kept logits sit), target, lse and delta, in column order, so the
-// backward kernels fetch a column's data in one contiguous round trip; and the
-// target entry of its logit-gradient row, G_{o} = delta (1 - p(o)), as
-// -delta expm1(l) with l = z_o - lse the token's log-prob (no cancellation as
-// p(o) -> 1).  A backward token has delta != 0, hence a forward column.
-__global__ __launch_bounds__(256) void gather_backward_kernel(int N, const int32_t* __restrict__ n_dev,
-                                                              const int32_t* __restrict__ act,
-                                                              const int32_t* __restrict__ fpos,
-                                                              const int32_t* __restrict__ target,
-                                                              const float* __restrict__ lse,
-                                                              const float* __restrict__ delta,
-                                                              const float* __restrict__ zt,
-                                                              int32_t* __restrict__ afwd, int32_t* __restrict__ ctgt,
-                                                              float* __restrict__ clse, float* __restrict__ cdelta,
-                                                              float* __restrict__ cg1) {
-  const int n = min(N, *n_dev);
-  for (int a = blockIdx.x * 256 + threadIdx.x; a < n; a += gridDim.x * 256) {
-    const int t = act[a];
-    const int f = fpos[t];
-    afwd[a] = f;
-    ctgt[a] = target[t];
-    clse[a] = lse[t];
-    cdelta[a] = delta[t];
-    cg1[a] = -delta[t] * expm1f(zt[f] - lse[t]);
-  }
-}
 
 // ---------------------------------------------------------------------------
 // Target entries of the logit gradient, g_i = G_{i,o_i} = delta_i (1 - p_i(o_i)),
@@ -1390,8 +1410,8 @@ int pspo_loss_fwd_bwd(const uint16_t* hidden, const uint16_t* w_head, const int3
 
   // 1. the tokens whose logits are needed (all of them if logp_new is wanted);
   //    W and their hidden rows as K-blocked operands
-  if (int rc = launch_compact(N, KeepForward{R, logp_new != nullptr ? 1 : 0, seq_id, advantage}, cnt, fwd_idx,
-                              fwd_pos, target, fwd_tgt, n_fwd, nullptr, stream))
+  if (int rc = launch_compact(N, KeepForward{R, logp_new != nullptr ? 1 : 0, seq_id, advantage},
+                              EmitForward{target, fwd_tgt}, cnt, fwd_idx, fwd_pos, n_fwd, nullptr, stream))
     return rc;
   // W K-blocked (forward and logit-gradient products) and, per vocabulary
   // chunk, W[chunk]^T (dH product), in one pass over W
@@ -1427,11 +1447,11 @@ int pspo_loss_fwd_bwd(const uint16_t* hidden, const uint16_t* w_head, const int3
   PSPO_LAUNCHED("reduce_loss_kernel", stream);
   // 4. the backward runs over the tokens with delta != 0 only (every other
   //    token has a zero logit-gradient row: zero d_hidden row, no dW term)
-  if (int rc = launch_compact(N, KeepActive{delta}, cnt, act_idx, nullptr, nullptr, nullptr, n_act, stats, stream))
+  if (int rc = launch_compact(N, KeepActive{delta},
+                              EmitBackward{fwd_pos, target, lse, delta, zt, act_fwd, act_tgt, act_lse, act_delta,
+                                           act_g1},
+                              cnt, act_idx, nullptr, n_act, stats, stream))
     return rc;
-  hipLaunchKernelGGL(gather_backward_kernel, dim3((unsigned)((pl.Npad + 255) / 256)), dim3(256), 0, stream, N, n_act,
-                     act_idx, fwd_pos, target, lse, delta, zt, act_fwd, act_tgt, act_lse, act_delta, act_g1);
-  PSPO_LAUNCHED("gather_backward_kernel", stream);
   hipLaunchKernelGGL(zero_inactive_rows_kernel, dim3((unsigned)N), dim3(256), 0, stream, d, delta, d_hidden);
   PSPO_LAUNCHED("zero_inactive_rows_kernel", stream);
   // 5. operands of the gradient products: the backward tokens' hidden rows
