@@ -164,7 +164,7 @@ int pspo_pack_prefixes(const int32_t* cutoffs, const int32_t* lengths,
                        hipStream_t stream);
 
 /*
- * Bytes of device workspace pspo_loss_fwd_bwd needs for N tokens (host-only,
+ * Bytes of device workspace pspo_loss_fwd_bwd needs for up to N tokens (host-only,
  * pure function of its arguments).
  */
 size_t pspo_loss_workspace_bytes(int32_t N, int32_t d, int32_t V, uint32_t flags);
@@ -194,8 +194,11 @@ size_t pspo_loss_workspace_bytes(int32_t N, int32_t d, int32_t V, uint32_t flags
  * The chunk width is about Vb = 384 * 256 / gcd(ceil(d / 256), 256) rows: the
  * vocabulary (padded to 384) is split evenly into floor(V / Vb) chunks, or one
  * more when the remainder exceeds Vb / 4 (one chunk if V < Vb), each a
- * multiple of 384 rows; three chunks of 50688 rows at d = 3584, V = 152064.  Every
- * result is deterministic (no floating-point atomics).
+ * multiple of 384 rows; three chunks of 50688 rows at d = 3584, V = 152064.
+ * Calls of at most 768 tokens without kept logits use one chunk (the size that
+ * pspo_loss_workspace_bytes() gives for any larger N covers that; in a workspace
+ * that only holds the chunks they run chunked).  Every result is deterministic
+ * (no floating-point atomics).
  *
  *  hidden     device, bf16 bits [N, d] row-major (packed prefix tokens).
  *  w_head     device, bf16 bits [V, d] row-major.

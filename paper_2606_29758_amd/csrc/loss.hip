@@ -1209,7 +1209,8 @@ struct Plan {
   bool keep;   // the forward keeps the first chunk's logits (fp16 offsets from the tile maxima)
 };
 
-Plan make_plan(int64_t N, int64_t d, int64_t V, bool keep) {
+// (one_chunk: the whole vocabulary as one backward chunk)
+Plan make_plan(int64_t N, int64_t d, int64_t V, bool keep, bool one_chunk) {
   Plan p{};
   p.Npad = round_up(N > 0 ? N : 1, kTileLcm);   // token rows: tiles of 256 (B side) and 384 (A side)
   p.Vpad = round_up(V, kTileM);
@@ -1235,7 +1236,7 @@ Plan make_plan(int64_t N, int64_t d, int64_t V, bool keep) {
     }
     const int64_t rows = 256 / a * kTileM;
     const int64_t whole = p.Vpad / rows, rem = p.Vpad % rows;
-    const int64_t nch = whole == 0 ? 1 : (rem * 4 <= rows ? whole : whole + 1);
+    const int64_t nch = whole == 0 || one_chunk ? 1 : (rem * 4 <= rows ? whole : whole + 1);
     p.Vc = round_up((p.Vpad + nch - 1) / nch, kTileM);
   }
   p.ntv = p.Vpad / kTileM;
@@ -1281,6 +1282,29 @@ Plan make_plan(int64_t N, int64_t d, int64_t V, bool keep) {
   return p;
 }
 
+// Calls of few tokens (one token block of 768) run the backward in one chunk when
+// the workspace has room for it: a chunk of theirs leaves most CUs idle (132 tiles
+// for 256 CUs at 200 tokens and V = 152064), and each costs its launches: 2,380 us
+// a call there in three chunks, 2,131 in one.
+// The logit gradient of the whole vocabulary then takes 2 x 768 x V x 2 bytes
+// (467 MB, next to 2.2 GB of operand copies of W, at d = 3584, V = 152064).  With
+// kept logits the plan stays chunked (the first chunk's are kept).
+Plan choose_plan(int64_t N, int64_t d, int64_t V, bool keep, size_t workspace_bytes) {
+  if (!keep && N <= kTileLcm) {
+    const Plan p = make_plan(N, d, V, keep, true);
+    if ((size_t)p.total <= workspace_bytes) return p;
+  }
+  return make_plan(N, d, V, keep, false);
+}
+
+// Bytes that any call of up to N tokens runs in, with the plan it would choose
+// given more: the size does not fall where the chunked plan begins.
+int64_t workspace_size(int64_t N, int64_t d, int64_t V, bool keep) {
+  const Plan chunked = make_plan(N, d, V, keep, false);
+  const int64_t kept = keep ? chunked.total - make_plan(N, d, V, false, false).total : 0;
+  return std::max(chunked.total, make_plan(std::min<int64_t>(N, kTileLcm), d, V, false, true).total + kept);
+}
+
 template <class Epi>
 int launch_gemm(const GemmShape& g, const Epi& epi, hipStream_t stream) {
   hipLaunchKernelGGL(gemm_nt_kernel<Epi>, dim3(gemm_grid(g.tiles_m, g.tiles_n)), dim3(kGemmThreads), 0, stream, g,
@@ -1294,13 +1318,16 @@ int launch_gemm(const GemmShape& g, const Epi& epi, hipStream_t stream) {
 // as `epi` would write them): the CUs stay busy through the last round.
 template <class Epi, class Out>
 int launch_gemm_split_tail(const GemmShape& g, const Epi& epi, const Out& out, float* slab, hipStream_t stream) {
-  hipLaunchKernelGGL((gemm_nt_kernel<Epi, kLaunchRounds>), dim3(gemm_grid(g.tiles_m, g.tiles_n)), dim3(kGemmThreads),
-                     0, stream, g, epi);
-  PSPO_LAUNCHED("gemm_nt_kernel (whole rounds)", stream);
+  const int per_xcd = (g.tiles_m * g.tiles_n + kNumXcd - 1) / kNumXcd;   // at most
+  if (per_xcd >= 32) {   // (otherwise there is no whole round)
+    hipLaunchKernelGGL((gemm_nt_kernel<Epi, kLaunchRounds>), dim3(gemm_grid(g.tiles_m, g.tiles_n)), dim3(kGemmThreads),
+                       0, stream, g, epi);
+    PSPO_LAUNCHED("gemm_nt_kernel (whole rounds)", stream);
+  }
   hipLaunchKernelGGL((gemm_nt_kernel<EpiSlab, kLaunchTail>), dim3(kNumXcd * kTailSlots), dim3(kGemmThreads), 0,
                      stream, g, EpiSlab{slab});
   PSPO_LAUNCHED("gemm_nt_kernel (K-split tail)", stream);
-  const int most = std::min((g.tiles_m * g.tiles_n + kNumXcd - 1) / kNumXcd, 31);   // of per_xcd % 32
+  const int most = std::min(per_xcd, 31);   // tail tiles of an XCD: per_xcd % 32
   hipLaunchKernelGGL(tail_reduce_kernel<Out>, dim3(kTileM / 16, (unsigned)(kNumXcd * most)), dim3(kTailThreads), 0, stream, g,
                      (const float*)slab, out);
   PSPO_LAUNCHED("tail_reduce_kernel", stream);
@@ -1314,7 +1341,7 @@ extern "C" {
 
 size_t pspo_loss_workspace_bytes(int32_t N, int32_t d, int32_t V, uint32_t flags) {
   if (N < 0 || d <= 0 || V <= 0) return 0;
-  return (size_t)pspo::make_plan(N, d, V, (flags & PSPO_KEEP_LOGITS) != 0).total;
+  return (size_t)pspo::workspace_size(N, d, V, (flags & PSPO_KEEP_LOGITS) != 0);
 }
 
 int pspo_loss_fwd_bwd(const uint16_t* hidden, const uint16_t* w_head, const int32_t* target, const float* logp_old,
@@ -1350,7 +1377,7 @@ int pspo_loss_fwd_bwd(const uint16_t* hidden, const uint16_t* w_head, const int3
                  "workspace must be non-NULL and 256-byte aligned");
   }
   if (stats) PSPO_REQUIRE(aligned(stats, 8), PSPO_ERR_INVALID_ARG, "misaligned stats");
-  const Plan pl = make_plan(N, d, V, (flags & PSPO_KEEP_LOGITS) != 0);
+  const Plan pl = choose_plan(N, d, V, (flags & PSPO_KEEP_LOGITS) != 0, workspace_bytes);
   PSPO_REQUIRE(pl.Npad <= kMaxPaddedRows && pl.Vpad <= kMaxPaddedRows, PSPO_ERR_UNSUPPORTED,
                "N and V must each be at most " + std::to_string(kMaxPaddedRows) + " rows after padding");
   PSPO_REQUIRE(d <= kMaxPaddedRows, PSPO_ERR_UNSUPPORTED,
