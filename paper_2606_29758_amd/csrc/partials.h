@@ -4,7 +4,7 @@
 // tile's maximum at part_m[k * ldp + col] and its sums relative to it.  They
 // are merged by blocks of kMergeThreads threads that take kMergeCols columns
 // with kMergeSlices threads each; slice s takes the tiles s, s + kMergeSlices,
-// ... in order and the slices are joined in a fixed tree, so the result depends
+// ... in order and the slices are joined in a fixed order, so the result depends
 // on the partials alone.  What bounds a merge is the latency of its loads: one
 // thread per column walked the 396 tiles of V = 152064 twice, with 1 block in
 // flight per 256 tokens (294 us for 2,048 tokens, 306 us for 200, 402 us for
