@@ -66,10 +66,11 @@ __device__ __forceinline__ double group_sum(double v) {
 // in order; each entry of a completion's list finds its token id's slot in a
 // hash table of the step in LDS (open addressing, at most half full) and adds
 // its signed probability there, so every id's terms are added in the order of the
-// completions; the next completion's entries are read one ahead.  One wave per step
+// completions; the entries of kListsAhead completions are read together.  One wave per step
 // compared every entry with every other one from LDS, and 8 of its lanes summed
 // the lists' masses with an exp per entry of their own: 160 us for 35,000
-// steps of 8 top-16 lists (19 MB of lists), 28 us now.
+// steps of 8 top-16 lists (19 MB of lists), 26 us now.
+constexpr int kListsAhead = 4;
 template <int G>
 __global__ __launch_bounds__(64) void design_weights_kernel(
     const float* __restrict__ gamma, const int32_t* __restrict__ topk_ids, const float* __restrict__ topk_logp,
@@ -90,12 +91,23 @@ __global__ __launch_bounds__(64) void design_weights_kernel(
   const int shift = __builtin_clz(slots) + 1;   // a hash's top log2(slots) bits
   const int64_t g = (int64_t)blockIdx.x * kSteps + lane / G;
   const bool live = g < total;
-  // prompt of g: the last p with xi_off[p] <= g
-  int lo = 0, hi = P - 1;
-  while (live && lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (xi_off[mid] <= g) lo = mid;
-    else hi = mid - 1;
+  // prompt of g: the last p with xi_off[p] <= g.  Up to 64 prompts: one load, and
+  // the offsets are counted by a ballot for each of the wave's steps (a binary
+  // search is a chain of loads, and a wave's time here is mostly load latency)
+  int lo = 0;
+  if (P <= 64) {
+    const int64_t off = lane < P ? xi_off[lane] : INT64_MAX;
+    for (int s = 0; s < kSteps; ++s) {
+      const int before = __popcll(__ballot(off <= (int64_t)blockIdx.x * kSteps + s));
+      if (lane / G == s) lo = max(before - 1, 0);
+    }
+  } else {
+    int hi = P - 1;
+    while (live && lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (xi_off[mid] <= g) lo = mid;
+      else hi = mid - 1;
+    }
   }
   const int p = lo;
   const int t = live ? (int)(g - xi_off[p]) + 1 : 0;
@@ -108,58 +120,62 @@ __global__ __launch_bounds__(64) void design_weights_kernel(
     bool succ = false;
     if (live && k0 + e < K) {
       const int r = p * K + k0 + e;
-      if (lengths[r] >= t) {
-        row = (int64_t)full_off[r] + t - 1;
-        succ = rewards[r] > 0.5f;
+      const int len = lengths[r], first = full_off[r];   // (loaded together)
+      const float reward = rewards[r];
+      if (len >= t) {
+        row = (int64_t)first + t - 1;
+        succ = reward > 0.5f;
         gsum += (double)gamma[row];
         nalive += 1.0;
         nsucc += succ ? 1.0 : 0.0;
       }
     }
     const int kn = min(G, K - k0);
-    int64_t cur = __shfl(row, 0, G);
-    int32_t id_next = -1;
-    float lp_next = 0.f;
-    if (cur >= 0 && e < topk) {
-      id_next = topk_ids[cur * topk + e];
-      lp_next = topk_logp[cur * topk + e];
-    }
-    for (int k = 0; k < kn; ++k) {
-      const int64_t now = cur;
-      int32_t id = id_next;
-      float lp = lp_next;
-      cur = k + 1 < kn ? __shfl(row, k + 1, G) : (int64_t)-1;
-      if (cur >= 0 && e < topk) {
-        id_next = topk_ids[cur * topk + e];
-        lp_next = topk_logp[cur * topk + e];
+    for (int kb = 0; kb < kn; kb += kListsAhead) {
+      int64_t rows[kListsAhead];
+      int32_t list_id[kListsAhead];
+      float list_lp[kListsAhead];
+#pragma unroll
+      for (int q = 0; q < kListsAhead; ++q) {
+        rows[q] = __shfl(row, min(kb + q, kn - 1), G);
+        if (kb + q >= kn) rows[q] = -1;
+        const bool on = rows[q] >= 0 && e < topk;
+        list_id[q] = on ? topk_ids[rows[q] * topk + e] : -1;
+        list_lp[q] = on ? topk_logp[rows[q] * topk + e] : 0.f;
       }
-      const double sign = __shfl((int)succ, k, G) ? 1.0 : -1.0;
-      double mass = 0.0;
-      if (now >= 0) {
-        for (int e1 = e;;) {
-          if (e1 < topk) {
-            const double pr = exp((double)lp);
-            mass += pr;
-            if (id >= 0) {
-              int slot = (int)((uint32_t)id * 0x9E3779B1u >> shift);
-              for (;;) {           // ends: the table has more slots than entries
-                const int32_t old = atomicCAS(&ids[slot], -1, id);
-                if (old == -1 || old == id) break;
-                slot = (slot + 1) & (slots - 1);
+#pragma unroll
+      for (int q = 0; q < kListsAhead; ++q) {
+        const int64_t now = rows[q];
+        int32_t id = list_id[q];
+        float lp = list_lp[q];
+        const double sign = __shfl((int)succ, min(kb + q, kn - 1), G) ? 1.0 : -1.0;
+        double mass = 0.0;
+        if (now >= 0) {
+          for (int e1 = e;;) {
+            if (e1 < topk) {
+              const double pr = exp((double)lp);
+              mass += pr;
+              if (id >= 0) {
+                int slot = (int)((uint32_t)id * 0x9E3779B1u >> shift);
+                for (;;) {           // ends: the table has more slots than entries
+                  const int32_t old = atomicCAS(&ids[slot], -1, id);
+                  if (old == -1 || old == id) break;
+                  slot = (slot + 1) & (slots - 1);
+                }
+                unsafeAtomicAdd(&sums[slot], sign * pr);   // (one row's ids may repeat)
               }
-              unsafeAtomicAdd(&sums[slot], sign * pr);   // (one row's ids may repeat)
+            }
+            e1 += G;
+            if (e1 - e >= topk) break;
+            if (e1 < topk) {         // lists longer than a wave
+              id = topk_ids[now * topk + e1];
+              lp = topk_logp[now * topk + e1];
             }
           }
-          e1 += G;
-          if (e1 - e >= topk) break;
-          if (e1 < topk) {         // lists longer than a wave
-            id = topk_ids[now * topk + e1];
-            lp = topk_logp[now * topk + e1];
-          }
         }
+        mass = group_sum<G>(mass);
+        if (now >= 0) rest += sign * fmax(0.0, 1.0 - mass);
       }
-      mass = group_sum<G>(mass);
-      if (now >= 0) rest += sign * fmax(0.0, 1.0 - mass);
     }
   }
   __syncthreads();
@@ -285,6 +301,7 @@ __device__ __forceinline__ void solve_prompt(const Blocks& bl, const double* wp,
   __shared__ int sh_saturated;
   __shared__ double sh_kappa;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+#pragma unroll 4
   for (int t = tid; t < n; t += kDesignThreads) {
     bl.ln[t] = 1;
     bl.wv[t] = wp[t];
@@ -402,6 +419,7 @@ __global__ __launch_bounds__(kDesignThreads) void design_cutoffs_kernel(
   __syncthreads();
   int n = 0;
   bool bad = false;
+#pragma unroll 4
   for (int t = tid; t < T; t += kDesignThreads) {
     const double v = wp[t];
     if (!(v >= 0.0) || isinf(v)) bad = true;
