@@ -309,7 +309,8 @@ enum {
  *  xi_off      device, int64 [P + 1]: the layout of the per-step outputs (the
  *              xi-table layout: xi_off[p+1] - xi_off[p] = T_p); total_T = xi_off[P]
  *              (host value, sizes the launch).
- *  1 <= K <= 64, topk >= 1, K * topk <= 256.
+ *  1 <= K <= 64, topk >= 1, K * topk <= 256; total_T < 2^26 at least (more for
+ *  lists of up to 32 entries; PSPO_ERR_UNSUPPORTED beyond one launch's threads).
  *  w           device, float64 [total_T] out; gamma_bar, u: device, float64
  *              [total_T] out, or NULL.
  *  err_flag    PSPO_DEVERR_BAD_XI if some step of a table has no alive

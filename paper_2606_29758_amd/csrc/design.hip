@@ -202,6 +202,9 @@ __global__ __launch_bounds__(64) void design_weights_kernel(
   }
 }
 
+// A launch takes fewer than 2^32 threads: one-wave blocks per launch.
+constexpr int64_t kMaxWaveBlocks = (int64_t(1) << 32) / 64 - 1;
+
 // Groups of G lanes: the smallest power of two >= topk (at least 4, at most 64)
 // whose 64 / G tables stay within 24 KB of LDS, so that six blocks or more share a CU.
 struct WeightsShape {
@@ -566,12 +569,14 @@ int pspo_design_weights(const float* gamma, const int32_t* topk_ids, const float
                "null pointer");
   PSPO_REQUIRE(aligned(w, 8) && aligned(gamma_bar, 8) && aligned(u, 8) && aligned(xi_off, 8), PSPO_ERR_INVALID_ARG,
                "misaligned float64 / int64 pointer");
-  if (int rc = require_gfx950()) return rc;
-  PSPO_REQUIRE((total_T + 3) / 4 <= INT32_MAX, PSPO_ERR_UNSUPPORTED, "problem too large");
   const WeightsShape shape = weights_shape(K, topk);
   const int steps = 64 / shape.group;
+  const int64_t blocks = total_T / steps + (total_T % steps != 0 ? 1 : 0);
+  PSPO_REQUIRE(blocks <= kMaxWaveBlocks, PSPO_ERR_UNSUPPORTED,
+               "problem too large: at most " + std::to_string(kMaxWaveBlocks * steps) + " steps at this K and topk");
+  if (int rc = require_gfx950()) return rc;
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((total_T + steps - 1) / steps)), dim3(64),
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64),
                        (unsigned)(steps * shape.slots * 12), stream, gamma, topk_ids, topk_logp, topk, lengths,
                        full_off, rewards, xi_off, P, K, total_T, shape.slots, w, gamma_bar, u, err_flag);
   };

@@ -241,6 +241,11 @@ def test_design_argument_errors(lib):
     assert weights(K=16, k=17) == UNSUPPORTED          # K * topk > 256
     assert weights(w=None) == INVALID
     assert weights(gb=ctypes.c_void_p((1 << 20) + 4)) == INVALID
+    # more work-groups of 64 threads than one launch takes (2^32 threads), at 16 steps a
+    # work-group (short lists), at one (lists of 33 entries and more), and past 32 bits
+    for K, k, T in ((2, 4, 16 * 2 ** 26), (2, 64, 2 ** 26), (1, 256, 2 ** 32 + 100), (8, 16, 2 ** 62)):
+        assert weights(K=K, k=k, T=T) == UNSUPPORTED, (K, k, T)
+        assert b"too large" in lib.pspo_last_error()
 
     def cutoffs(**kw):
         T = kw.get("T", 100)
