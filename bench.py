@@ -61,15 +61,31 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "loss_fwd_bwd_qwen7b_traffic.json"
 XI_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "computing_xi_qwen7b_traffic.json")
 
 
-def source_hash():
-    """Digest of the HIP/C++ sources of libpspo with comments and whitespace removed
-    (identifies the kernels counters were taken on; a comment edit changes no kernel)."""
+CSRC = os.path.join(ROOT, "paper_2606_29758_amd", "csrc")
+
+
+def source_files(source):
+    """The files of csrc that `source` is compiled from: itself and what it includes by quotes."""
+    import re
+    files, todo = set(), [source]
+    while todo:
+        name = todo.pop()
+        if name in files or not os.path.exists(os.path.join(CSRC, name)):
+            continue
+        files.add(name)
+        with open(os.path.join(CSRC, name), encoding="utf-8") as f:
+            todo += re.findall(r'^\s*#include\s+"([^"]+)"', f.read(), flags=re.M)
+    return sorted(files)
+
+
+def source_hash(source):
+    """Digest of the files that `source` (loss.hip or proxy.hip, whose kernels were counted) is
+    compiled from, with comments and whitespace removed (a comment edit changes no kernel)."""
     import hashlib
     import re
     h = hashlib.sha256()
-    csrc = os.path.join(ROOT, "paper_2606_29758_amd", "csrc")
-    for name in sorted(os.listdir(csrc)):
-        with open(os.path.join(csrc, name), encoding="utf-8") as f:
+    for name in source_files(source):
+        with open(os.path.join(CSRC, name), encoding="utf-8") as f:
             text = f.read()
         text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)
         text = re.sub(r"//[^\n]*", " ", text)
@@ -278,7 +294,7 @@ def bench_proxy(args):
     if os.path.exists(XI_TRAFFIC_FILE):
         with open(XI_TRAFFIC_FILE) as f:
             t = json.load(f)
-        if t.get("N") == N and t.get("workload") == args.workload and t.get("source_hash") == source_hash():
+        if t.get("N") == N and t.get("workload") == args.workload and t.get("source_hash") == source_hash("proxy.hip"):
             traffic = t["bytes_per_launch"]
             counters = {"source": os.path.relpath(XI_TRAFFIC_FILE, ROOT) + " (rocprofv3 --pmc runs of the same "
                                                                            "kernel on this batch, not re-measured here)",
@@ -472,7 +488,7 @@ def main():
     if os.path.exists(TRAFFIC_FILE):
         with open(TRAFFIC_FILE) as f:
             t = json.load(f)
-        if t.get("N") == N and t.get("workload") == args.workload and t.get("source_hash") == source_hash():
+        if t.get("N") == N and t.get("workload") == args.workload and t.get("source_hash") == source_hash("loss.hip"):
             traffic = t.get("bytes_per_call")
             fwd_traffic = t["per_kernel_fetch_bytes"]["EpiForward"] + t["per_kernel_write_bytes"]["EpiForward"]
             # rocprofv3 counters of the same kernels and batch (committed under profiles/):

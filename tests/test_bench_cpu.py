@@ -1,6 +1,6 @@
 """bench.py's host-side contract without a GPU: more than one GPU is refused with a
-message that says why, and the source digest that gates the committed counters
-ignores comments and whitespace but not code."""
+message that says why, and the digest that gates the committed counters covers the
+files that the counted kernels are compiled from, and only those."""
 import importlib.util
 import json
 import os
@@ -29,7 +29,16 @@ def test_committed_counters_match_the_sources():
     """The committed counter files name the sources they were taken on; while they match, the
     bench lines carry their memory-side bytes (a mismatch would silently drop them)."""
     b = _bench()
-    digest = b.source_hash()
-    for name in ("loss_fwd_bwd_qwen7b_traffic.json", "computing_xi_qwen7b_traffic.json"):
+    for name, source in (("loss_fwd_bwd_qwen7b_traffic.json", "loss.hip"),
+                         ("computing_xi_qwen7b_traffic.json", "proxy.hip")):
         with open(os.path.join(ROOT, "profiles", name)) as f:
-            assert json.load(f)["source_hash"] == digest, name
+            assert json.load(f)["source_hash"] == b.source_hash(source), name
+
+
+def test_counter_digest_covers_the_counted_kernels():
+    """A change outside the files a counted kernel is compiled from leaves its counters valid (a
+    digest of every source asked for a new stamp on counters that had not been taken again)."""
+    b = _bench()
+    shared = ["common.h", "gemm.h", "layout.h", "partials.h", "rowdot.h"]
+    assert b.source_files("loss.hip") == sorted(shared + ["loss.hip"])
+    assert b.source_files("proxy.hip") == sorted(shared + ["proxy.hip"])
