@@ -61,14 +61,67 @@ __device__ __forceinline__ double group_sum(double v) {
   return v;
 }
 
+__device__ __forceinline__ double lane_value(double x, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// The prompt of step g: the last p with xi_off[p] <= g (0 if none).  Called by a
+// whole wave whose steps are first + (lane * kSteps / 64).  Up to 64 prompts: one
+// load, and the offsets are counted by a ballot for each of the wave's steps (a
+// binary search is a chain of loads, and a wave's time in the weights' kernels is
+// mostly load latency).
+template <int kSteps>
+__device__ __forceinline__ int prompt_of(const int64_t* __restrict__ xi_off, int P, int64_t total, int64_t first) {
+  const int lane = threadIdx.x & 63, mine = lane / (64 / kSteps);
+  int lo = 0;
+  if (P <= 64) {
+    const int64_t off = lane < P ? xi_off[lane] : INT64_MAX;
+    for (int s = 0; s < kSteps; ++s) {
+      const int before = __popcll(__ballot(off <= first + s));
+      if (mine == s) lo = max(before - 1, 0);
+    }
+  } else {
+    const int64_t g = first + mine;
+    int hi = P - 1;
+    while (g < total && lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (xi_off[mid] <= g) lo = mid;
+      else hi = mid - 1;
+    }
+  }
+  return lo;
+}
+
+// The outputs of step g from its sums over the alive completions.
+__device__ __forceinline__ void write_weight(int64_t g, double gsum, double nalive, double nsucc, double l1,
+                                             double rest, double* __restrict__ w, double* __restrict__ gbar_out,
+                                             double* __restrict__ u_out, int32_t* __restrict__ err_flag) {
+  if (nalive == 0.0) {   // the table is longer than every completion of the prompt
+    if (err_flag) atomicOr(err_flag, PSPO_DEVERR_BAD_XI);
+    w[g] = NAN;
+    return;
+  }
+  const double gb = gsum / nalive;
+  // equal rewards among the alive completions: p is 0 or 1 and the norm is exactly 1,
+  // so u = 0 (taken exactly); otherwise ||.||_1 <= 1 by the triangle inequality, so
+  // u >= 0 and rounding below it is clamped
+  const double u = (nsucc == 0.0 || nsucc == nalive) ? 0.0 : fmax(0.0, 0.5 - 0.5 * (l1 + fabs(rest)) / nalive);
+  w[g] = gb * u;
+  if (gbar_out) gbar_out[g] = gb;
+  if (u_out) u_out[g] = u;
+}
+
 // The weights: a group of G lanes (a power of two >= topk, up to 64) per
 // (prompt, step), 64 / G steps per one-wave block.  The completions are taken
 // in order; each entry of a completion's list finds its token id's slot in a
 // hash table of the step in LDS (open addressing, at most half full) and adds
 // its signed probability there, so every id's terms are added in the order of the
-// completions; the entries of kListsAhead completions are read together.  One wave per step
-// compared every entry with every other one from LDS, and 8 of its lanes summed
-// the lists' masses with an exp per entry of their own: 160 us for 35,000
+// completions; the entries of kListsAhead completions are read together.  One wave
+// per step compared every entry with every other one from LDS, and 8 of its lanes
+// summed the lists' masses with an exp per entry of their own: 160 us for 35,000
 // steps of 8 top-16 lists (19 MB of lists), 26 us now.
 constexpr int kListsAhead = 4;
 template <int G>
@@ -91,25 +144,7 @@ __global__ __launch_bounds__(64) void design_weights_kernel(
   const int shift = __builtin_clz(slots) + 1;   // a hash's top log2(slots) bits
   const int64_t g = (int64_t)blockIdx.x * kSteps + lane / G;
   const bool live = g < total;
-  // prompt of g: the last p with xi_off[p] <= g.  Up to 64 prompts: one load, and
-  // the offsets are counted by a ballot for each of the wave's steps (a binary
-  // search is a chain of loads, and a wave's time here is mostly load latency)
-  int lo = 0;
-  if (P <= 64) {
-    const int64_t off = lane < P ? xi_off[lane] : INT64_MAX;
-    for (int s = 0; s < kSteps; ++s) {
-      const int before = __popcll(__ballot(off <= (int64_t)blockIdx.x * kSteps + s));
-      if (lane / G == s) lo = max(before - 1, 0);
-    }
-  } else {
-    int hi = P - 1;
-    while (live && lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (xi_off[mid] <= g) lo = mid;
-      else hi = mid - 1;
-    }
-  }
-  const int p = lo;
+  const int p = prompt_of<kSteps>(xi_off, P, total, (int64_t)blockIdx.x * kSteps);
   const int t = live ? (int)(g - xi_off[p]) + 1 : 0;
   __syncthreads();
 
@@ -185,25 +220,118 @@ __global__ __launch_bounds__(64) void design_weights_kernel(
   gsum = group_sum<G>(gsum);
   nalive = group_sum<G>(nalive);
   nsucc = group_sum<G>(nsucc);
-  if (live && e == 0) {
-    if (nalive == 0.0) {   // the table is longer than every completion of the prompt
-      if (err_flag) atomicOr(err_flag, PSPO_DEVERR_BAD_XI);
-      w[g] = NAN;
-      return;
+  if (live && e == 0) write_weight(g, gsum, nalive, nsucc, l1, rest, w, gbar_out, u_out, err_flag);
+}
+
+// The weights where many lists have few entries: a wave per step, entry j = k topk + i
+// of its K lists in lane j % 64 (E entries a lane), the entries of an id found by a
+// ballot: the order of every sum is that of the entries.
+template <int E>
+__global__ __launch_bounds__(64) void design_weights_short_kernel(
+    const float* __restrict__ gamma, const int32_t* __restrict__ topk_ids, const float* __restrict__ topk_logp,
+    int topk, const int32_t* __restrict__ lengths, const int32_t* __restrict__ full_off,
+    const float* __restrict__ rewards, const int64_t* __restrict__ xi_off, int P, int K, int64_t total,
+    double* __restrict__ w, double* __restrict__ gbar_out, double* __restrict__ u_out, int32_t* __restrict__ err_flag) {
+  const int lane = threadIdx.x;
+  const int64_t g = blockIdx.x;
+  const int p = prompt_of<1>(xi_off, P, total, g);
+  const int t = (int)(g - xi_off[p]) + 1;
+  // lane k: the row of completion k at this step (-1: not alive)
+  int64_t row = -1;
+  double gsum = 0.0;
+  bool succ = false;
+  if (lane < K) {
+    const int r = p * K + lane;
+    const int len = lengths[r], first = full_off[r];
+    const float reward = rewards[r];
+    if (len >= t) {
+      row = (int64_t)first + t - 1;
+      gsum = (double)gamma[row];
+      succ = reward > 0.5f;
     }
-    const double gb = gsum / nalive;
-    // equal rewards among the alive completions: p is 0 or 1 and the norm is exactly 1,
-    // so u = 0 (taken exactly); otherwise ||.||_1 <= 1 by the triangle inequality, so
-    // u >= 0 and rounding below it is clamped
-    const double u = (nsucc == 0.0 || nsucc == nalive) ? 0.0 : fmax(0.0, 0.5 - 0.5 * (l1 + fabs(rest)) / nalive);
-    w[g] = gb * u;
-    if (gbar_out) gbar_out[g] = gb;
-    if (u_out) u_out[g] = u;
   }
+  const uint64_t alive = __ballot(row >= 0), good = __ballot(succ);
+  const int ne = K * topk;
+  int32_t id[E];
+  double pr[E], v[E];
+#pragma unroll
+  for (int u = 0; u < E; ++u) {
+    const int j = lane + 64 * u, k = min(j / topk, 63);
+    const int64_t from = __shfl(row, k);
+    const bool on = j < ne && from >= 0;
+    id[u] = on ? topk_ids[from * topk + (j - k * topk)] : -1;
+    pr[u] = on ? exp((double)topk_logp[from * topk + (j - k * topk)]) : 0.0;
+    v[u] = good >> k & 1 ? pr[u] : -pr[u];
+  }
+  // lane k: the mass outside its completion's list
+  double mass = 0.0;
+  for (int i = 0; i < topk; ++i) {
+    const int j = lane * topk + i;
+    double x = __shfl(pr[0], j & 63);
+    if constexpr (E > 1) {
+      const double y = __shfl(pr[1], j & 63);
+      x = j < 64 ? x : y;
+    }
+    mass += x;
+  }
+  double rest = row >= 0 ? (succ ? 1.0 : -1.0) * fmax(0.0, 1.0 - mass) : 0.0;
+  // each distinct id once: an id of one entry is that entry's value already; the
+  // values of a repeated one are added in the order of the entries, for its first
+  double sum[E];
+  uint64_t left[E];
+#pragma unroll
+  for (int u = 0; u < E; ++u) {
+    sum[u] = id[u] >= 0 ? v[u] : 0.0;
+    left[u] = __ballot(id[u] >= 0);
+  }
+#pragma unroll
+  for (int q = 0; q < E; ++q) {
+    while (left[q] != 0) {
+      const int i = __builtin_ctzll(left[q]);
+      const int32_t other = __builtin_amdgcn_readlane(id[q], i);
+      uint64_t same[E];
+      int n = 0;
+#pragma unroll
+      for (int u = 0; u < E; ++u) {
+        same[u] = __ballot(id[u] == other);
+        left[u] &= ~same[u];
+        n += __popcll(same[u]);
+      }
+      if (n == 1) continue;   // uniform over the wave
+      double x = 0.0;
+#pragma unroll
+      for (int u = 0; u < E; ++u) {
+        for (uint64_t m = same[u]; m != 0; m &= m - 1) x += lane_value(v[u], __builtin_ctzll(m));
+        if (id[u] == other) sum[u] = 0.0;
+      }
+      if (lane == i) sum[q] = x;
+    }
+  }
+  double l1 = 0.0;
+#pragma unroll
+  for (int u = 0; u < E; ++u) l1 += fabs(sum[u]);
+  l1 = wave_sum(l1);
+  rest = wave_sum(rest);
+  gsum = wave_sum(gsum);
+  if (lane == 0)
+    write_weight(g, gsum, (double)__popcll(alive), (double)__popcll(good), l1, rest, w, gbar_out, u_out, err_flag);
 }
 
 // A launch takes fewer than 2^32 threads: one-wave blocks per launch.
 constexpr int64_t kMaxWaveBlocks = (int64_t(1) << 32) / 64 - 1;
+
+// Whether a step's entries are compared within a wave (design_weights_short_kernel)
+// rather than gathered in its table: many lists of few entries, which a group of four
+// lanes passes four at a time (0.7 us a completion, however few the steps), while a
+// wave per step takes 5 us and, past some 5,000 steps, 0.5 to 1.9 ns a step.  us a
+// call, table / wave: 8 lists of 1 entry 7.4 / 4.7 at 16 steps and 8.5 / 9.6 at 15,582;
+// 16 of 4 18.6 / 6.3 at 1,961 and 20.7 / 17.1 at 15,752; 24 of 1 22.9 / 21.1 at 31,462;
+// 64 of 1 103.8 / 32.2 at 31,766; 64 of 2 52.2 / 10.3 at 1,989.  Up to four lists
+// the table is as fast at any number of steps (4.8 to 7.1).
+inline bool short_lists_pay(int K, int topk, int64_t total_T) {
+  if (K <= 4 || topk > 4 || K * topk > 128) return false;
+  return total_T <= (K >= 24 ? kMaxWaveBlocks : 1300 * K);
+}
 
 // Groups of G lanes: the smallest power of two >= topk (at least 4, at most 64)
 // whose 64 / G tables stay within 24 KB of LDS, so that six blocks or more share a CU.
@@ -290,13 +418,6 @@ __device__ __forceinline__ void mark_heads(const Blocks& bl, int n) {
     const uint64_t m = __ballot(t < n && bl.ln[t] > 0);
     if ((threadIdx.x & 63) == 0) bl.heads[t / 64] = m;
   }
-}
-
-__device__ __forceinline__ double lane_value(double x, int lane) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, x);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
-  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
 }
 
 // The solve of one prompt of T steps whose last positive weight is step n - 1
@@ -569,22 +690,26 @@ int pspo_design_weights(const float* gamma, const int32_t* topk_ids, const float
                "null pointer");
   PSPO_REQUIRE(aligned(w, 8) && aligned(gamma_bar, 8) && aligned(u, 8) && aligned(xi_off, 8), PSPO_ERR_INVALID_ARG,
                "misaligned float64 / int64 pointer");
+  const int ne = K * topk;
+  const bool few = short_lists_pay(K, topk, total_T);
   const WeightsShape shape = weights_shape(K, topk);
-  const int steps = 64 / shape.group;
+  const int steps = few ? 1 : 64 / shape.group;
   const int64_t blocks = total_T / steps + (total_T % steps != 0 ? 1 : 0);
   PSPO_REQUIRE(blocks <= kMaxWaveBlocks, PSPO_ERR_UNSUPPORTED,
                "problem too large: at most " + std::to_string(kMaxWaveBlocks * steps) + " steps at this K and topk");
   if (int rc = require_gfx950()) return rc;
-  auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64),
-                       (unsigned)(steps * shape.slots * 12), stream, gamma, topk_ids, topk_logp, topk, lengths,
-                       full_off, rewards, xi_off, P, K, total_T, shape.slots, w, gamma_bar, u, err_flag);
+  auto launch = [&](auto kernel, auto... slots) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64), few ? 0u : (unsigned)(steps * shape.slots * 12), stream,
+                       gamma, topk_ids, topk_logp, topk, lengths, full_off, rewards, xi_off, P, K, total_T, slots..., w,
+                       gamma_bar, u, err_flag);
   };
-  if (shape.group == 4) launch(design_weights_kernel<4>);
-  else if (shape.group == 8) launch(design_weights_kernel<8>);
-  else if (shape.group == 16) launch(design_weights_kernel<16>);
-  else if (shape.group == 32) launch(design_weights_kernel<32>);
-  else launch(design_weights_kernel<64>);
+  if (few && ne <= 64) launch(design_weights_short_kernel<1>);
+  else if (few) launch(design_weights_short_kernel<2>);
+  else if (shape.group == 4) launch(design_weights_kernel<4>, shape.slots);
+  else if (shape.group == 8) launch(design_weights_kernel<8>, shape.slots);
+  else if (shape.group == 16) launch(design_weights_kernel<16>, shape.slots);
+  else if (shape.group == 32) launch(design_weights_kernel<32>, shape.slots);
+  else launch(design_weights_kernel<64>, shape.slots);
   PSPO_LAUNCHED("design_weights_kernel", stream);
   return PSPO_OK;
 }

@@ -1,7 +1,8 @@
 """GPU: the design weights over the list shapes that choose the group width (lists of 1 to 256 entries,
-1 to 64 completions, up to 256 entries a step), step counts that leave groups and blocks part empty,
-lists that share all their ids (every table slot summed K times), none, or repeat one, and ids past the
-table's size.
+1 to 64 completions, up to 256 entries a step) or the wave per step (5 completions or more with lists of
+up to 4 entries, up to 128 a step: one and two entries a lane, both sides of each limit), step counts that
+leave groups and blocks part empty, lists that share all their ids (every table slot summed K times),
+none, or repeat one, and ids past the table's size.
 
 Both sides add the same float64 terms in another order: at most 256 terms of at most 1, so 1e-13.
 """
@@ -14,7 +15,7 @@ from paper_2606_29758_amd import pspo
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(1, 1), (64, 1), (64, 4), (2, 3), (5, 7), (8, 8), (8, 16), (16, 16), (9, 17), (4, 64), (3, 65), (3, 85),
-          (2, 128), (1, 256)]
+          (2, 128), (1, 256), (4, 4), (5, 1), (5, 4), (5, 5), (16, 4), (23, 1), (24, 1), (32, 4), (33, 3), (43, 3), (64, 2)]
 
 
 def _reference(gamma, ids, logp, lengths, rewards, P, K):
