@@ -119,7 +119,11 @@ __device__ __forceinline__ void write_weight(int64_t g, double gsum, double nali
 // in order; each entry of a completion's list finds its token id's slot in a
 // hash table of the step in LDS (open addressing, at most half full) and adds
 // its signed probability there, so every id's terms are added in the order of the
-// completions; the entries of kListsAhead completions are read together.  One wave
+// completions; the entries of kListsAhead completions are read together.  Two orders
+// rest on the wave, whose LDS atomics the hardware carries out lane by lane, always in
+// the same order, and on the table being this wave's alone: which of two new ids of
+// one list that meet in a slot takes it (the final sum goes through the slots), and
+// the terms of an id that one list holds twice.  So a call repeats its bits.  One wave
 // per step compared every entry with every other one from LDS, and 8 of its lanes
 // summed the lists' masses with an exp per entry of their own: 160 us for 35,000
 // steps of 8 top-16 lists (19 MB of lists), 26 us now.
