@@ -167,11 +167,22 @@ __global__ void pack_fill_kernel(const int32_t* __restrict__ cu_seqlens, const i
   }
 }
 
-// Copies the kept hidden rows: one wave per row, 16 bytes per lane, kPieces loads
-// in flight before their stores; the copy is read by later kernels from memory, so
-// both go past the caches.  One load at a time and its store, through the caches:
-// 688 us for the sampling and packing of 32 completions of up to 16,384 tokens,
-// d = 3584 (2.8 GB moved); now 625 us, 4.5 TB/s.
+// Copies the kept hidden rows, one wave per row, 16 bytes per lane.  When the rows
+// read and written together exceed the memory-side cache (256 MB), a row's next
+// kPieces loads go out before their stores and both go past the caches, which could not
+// serve the copy's reader: sampling and packing 32 completions of up to 16,384 tokens,
+// d = 3584 (2.8 GB moved), one load at a time through the caches 688 us, so 625 us,
+// 4.5 TB/s.  A smaller copy goes through the caches, from which the next call reads
+// it (past them / through them: 5,676 rows of d = 3584 23.3 / 20.8 us, 56,843 of
+// d = 1024 51.2 / 44.8, 90,763 of d = 512 138.8 / 126.6; above the line 90,083 of
+// d = 768 164.4 / 195.2, 139,930 of d = 520 72.8 / 79.5), and so do rows of fewer
+// pieces than lanes, which the caches join to whole lines.  kLarge: the capacity
+// leaves it open which of the two it is; otherwise through the caches.
+constexpr int64_t kMemorySideBytes = int64_t(256) << 20;
+__host__ __device__ inline bool pack_passes(int64_t rows, int32_t vec_per_row) {
+  return vec_per_row >= 64 && rows * vec_per_row * (2 * (int64_t)sizeof(u32x4)) > kMemorySideBytes;
+}
+template <bool kLarge>
 __global__ __launch_bounds__(256) void pack_hidden_kernel(const int32_t* __restrict__ cu_seqlens,
                                                           const int32_t* __restrict__ full_off, int32_t capacity,
                                                           const u32x4* __restrict__ hidden_full,
@@ -179,22 +190,31 @@ __global__ __launch_bounds__(256) void pack_hidden_kernel(const int32_t* __restr
   constexpr int kPieces = 8;
   const int r = blockIdx.y;
   const int32_t c0 = cu_seqlens[r], H = cu_seqlens[r + 1] - c0;
-  const int32_t f0 = full_off[r];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int waves = blockDim.x >> 6;
+  bool past = false;
+  if constexpr (kLarge) {
+    if (blockIdx.x * waves >= H) return;   // (most blocks, where completions are short)
+    past = pack_passes(min(cu_seqlens[gridDim.y], capacity), vec_per_row);
+  }
+  const int32_t f0 = full_off[r];
   for (int j = blockIdx.x * waves + wave; j < H; j += gridDim.x * waves) {
     const int64_t i = (int64_t)c0 + j;
     if (i >= capacity) break;
     const u32x4* src = hidden_full + (int64_t)(f0 + j) * vec_per_row;
     u32x4* dst = hidden + i * vec_per_row;
-    for (int b = lane; b < vec_per_row; b += 64 * kPieces) {
-      u32x4 x[kPieces];
+    if (past) {
+      for (int b = lane; b < vec_per_row; b += 64 * kPieces) {
+        u32x4 x[kPieces];
 #pragma unroll
-      for (int q = 0; q < kPieces; ++q)
-        if (b + 64 * q < vec_per_row) x[q] = __builtin_nontemporal_load(src + b + 64 * q);
+        for (int q = 0; q < kPieces; ++q)
+          if (b + 64 * q < vec_per_row) x[q] = __builtin_nontemporal_load(src + b + 64 * q);
 #pragma unroll
-      for (int q = 0; q < kPieces; ++q)
-        if (b + 64 * q < vec_per_row) __builtin_nontemporal_store(x[q], dst + b + 64 * q);
+        for (int q = 0; q < kPieces; ++q)
+          if (b + 64 * q < vec_per_row) __builtin_nontemporal_store(x[q], dst + b + 64 * q);
+      }
+    } else {
+      for (int b = lane; b < vec_per_row; b += 64) dst[b] = src[b];
     }
   }
 }
@@ -266,8 +286,9 @@ int pspo_pack_prefixes(const int32_t* cutoffs, const int32_t* lengths, const dou
                      capacity, target_full, logp_old_full, src_row, seq_id, weight, target, logp_old);
   PSPO_LAUNCHED("pack_fill_kernel", stream);
   if (hidden_full) {
-    hipLaunchKernelGGL(pack_hidden_kernel, dim3(64, R), dim3(256), 0, stream, cu_seqlens, full_off, capacity,
-                       reinterpret_cast<const u32x4*>(hidden_full), reinterpret_cast<u32x4*>(hidden), d / 8);
+    hipLaunchKernelGGL(pack_passes(capacity, d / 8) ? pack_hidden_kernel<true> : pack_hidden_kernel<false>, dim3(64, R),
+                       dim3(256), 0, stream, cu_seqlens, full_off, capacity, reinterpret_cast<const u32x4*>(hidden_full),
+                       reinterpret_cast<u32x4*>(hidden), d / 8);
     PSPO_LAUNCHED("pack_hidden_kernel", stream);
   }
   return PSPO_OK;
