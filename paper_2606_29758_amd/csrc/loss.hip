@@ -772,40 +772,41 @@ __device__ __forceinline__ float half_max(float v) {
 // Per token: merge the vocabulary-tile partials into lse, then the PPO terms.
 // Each block (kMergeCols tokens) writes (sum c s, sum |c s|, #clipped, #A==0)
 // and max c to blk[5*b].  The tiles' terms are loaded and scaled by all slices,
-// kMergeTiles at a time, and added in tile order by one thread per token from LDS
+// 4 per slice at a time, and added in tile order by one thread per token from LDS
 // (two LDS reads and an fma a tile, 1.5 us for 396 tiles): the loss is a signed sum
 // over tokens, often 30 times smaller than its terms, so the order in which a
 // token's rounding falls shows in it.
-constexpr int kMergeTiles = 4 * kMergeSlices;
-__global__ __launch_bounds__(kMergeThreads) void finalize_kernel(
+template <int kSlices>
+__global__ __launch_bounds__(kMergeCols * kSlices) void finalize_kernel(
     int N, int V, int R, int ntv, int64_t ldp, const float* __restrict__ part_m, const float* __restrict__ part_l,
     const float* __restrict__ zt, const int32_t* __restrict__ fwd_pos, const int32_t* __restrict__ target,
     const float* __restrict__ logp_old,
     const float* __restrict__ weight, const int32_t* __restrict__ seq_id, const float* __restrict__ adv,
     float eps_low, float eps_high, float loss_scale, float* __restrict__ lse_out, float* __restrict__ delta_out,
     float* __restrict__ logp_new, double* __restrict__ blk, int32_t* __restrict__ err_flag) {
-  __shared__ MergeRow sh[kMergeSlices];
+  constexpr int kMergeTiles = 4 * kSlices;
+  __shared__ MergeRow sh[kSlices];
   __shared__ MergeRow tile_l[kMergeTiles], tile_e[kMergeTiles];
   const int c = threadIdx.x % kMergeCols, slice = threadIdx.x / kMergeCols;
   const int t = blockIdx.x * kMergeCols + c;
   // column of this token's forward partials; -1: its logits were not needed
   const int col = t < N ? fwd_pos[t] : -1;
-  const float M = merge_max(part_m, ntv, ldp, col, sh);
+  const float M = merge_max<kSlices>(part_m, ntv, ldp, col, sh);
   float L = 0.f;
   for (int k0 = 0; k0 < ntv; k0 += kMergeTiles) {
     const int kn = min(ntv - k0, kMergeTiles);
     float m[4], l[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int k = slice + e * kMergeSlices;
+      const int k = slice + e * kSlices;
       const bool on = col >= 0 && k < kn;
       m[e] = on ? part_m[(k0 + k) * ldp + col] : 0.f;
       l[e] = on ? part_l[(k0 + k) * ldp + col] : 0.f;
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      tile_l[slice + e * kMergeSlices][c] = l[e];
-      tile_e[slice + e * kMergeSlices][c] = __expf(m[e] - M);
+      tile_l[slice + e * kSlices][c] = l[e];
+      tile_e[slice + e * kSlices][c] = __expf(m[e] - M);
     }
     __syncthreads();
     if (slice == 0) {
@@ -1485,9 +1486,11 @@ int pspo_loss_fwd_bwd(const uint16_t* hidden, const uint16_t* w_head, const int3
                      fwd_idx, fwd_tgt, n_fwd, zt, nullptr);
   PSPO_LAUNCHED("row_dots_kernel", stream);
   // 3. lse, PPO terms, delta, loss
-  hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)pl.nfin), dim3(kMergeThreads), 0, stream, N, V, R, tiles_voc,
-                     pl.Npad, part_m, part_l, zt, fwd_pos, target, logp_old, weight, seq_id, advantage, eps_low,
-                     eps_high, loss_scale, lse, delta, logp_new, blk, err_flag);
+  merge_variant(tiles_voc, [&](auto slices) {
+    hipLaunchKernelGGL(finalize_kernel<slices.value>, dim3((unsigned)pl.nfin), dim3(kMergeCols * slices.value), 0, stream,
+                       N, V, R, tiles_voc, pl.Npad, part_m, part_l, zt, fwd_pos, target, logp_old, weight, seq_id,
+                       advantage, eps_low, eps_high, loss_scale, lse, delta, logp_new, blk, err_flag);
+  });
   PSPO_LAUNCHED("finalize_kernel", stream);
   hipLaunchKernelGGL(reduce_loss_kernel, dim3(1), dim3(kFinThreads), 0, stream, (int)pl.nfin, blk, loss_scale,
                      loss, stats);

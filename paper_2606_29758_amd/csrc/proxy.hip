@@ -140,26 +140,27 @@ struct EpiProxy {
 };
 
 // Merge the vocabulary-tile partials of each token and form gamma, log p(o), ||p||^2.
-__global__ __launch_bounds__(kMergeThreads) void proxy_finalize_kernel(
+template <int kSlices>
+__global__ __launch_bounds__(kMergeCols * kSlices) void proxy_finalize_kernel(
     int N, int V, int ntv, int64_t ldp, const float* __restrict__ part_m, const float* __restrict__ part_s1,
     const float* __restrict__ part_s2, const float* __restrict__ zt, const float* __restrict__ hn,
     const int32_t* __restrict__ target, float* __restrict__ gamma, float* __restrict__ logp, float* __restrict__ p_sq,
     int32_t* __restrict__ err_flag) {
-  __shared__ MergeRow sh[kMergeSlices];
+  __shared__ MergeRow sh[kSlices];
   const int t = blockIdx.x * kMergeCols + threadIdx.x % kMergeCols;
   const int col = t < N ? t : -1;
-  const float M = merge_max(part_m, ntv, ldp, col, sh);
+  const float M = merge_max<kSlices>(part_m, ntv, ldp, col, sh);
   float s1 = 0.f, s2 = 0.f;
   if (col >= 0) {
 #pragma unroll 4
-    for (int k = threadIdx.x / kMergeCols; k < ntv; k += kMergeSlices) {
+    for (int k = threadIdx.x / kMergeCols; k < ntv; k += kSlices) {
       const float m = part_m[k * ldp + t], a = part_s1[k * ldp + t], b = part_s2[k * ldp + t];
       const float f = m != kNegInf ? __expf(m - M) : 0.f;
       s1 += a * f;
       s2 += b * f * f;
     }
   }
-  const float S1 = merge_sum(s1, sh), S2 = merge_sum(s2, sh);
+  const float S1 = merge_sum<kSlices>(s1, sh), S2 = merge_sum<kSlices>(s2, sh);
   if (threadIdx.x >= kMergeCols || t >= N) return;
   const int tgt = target[t];
   if (tgt < 0 || tgt >= V) {
@@ -272,8 +273,11 @@ int pspo_score_proxy(const uint16_t* hidden, const uint16_t* w_head, const int32
   hipLaunchKernelGGL(row_dots_kernel, dim3((unsigned)((N + 3) / 4)), dim3(256), 0, stream, hidden, w_head, d, V, N,
                      nullptr, target, nullptr, zt, hn);
   PSPO_LAUNCHED("row_dots_kernel", stream);
-  hipLaunchKernelGGL(proxy_finalize_kernel, dim3((unsigned)((N + kMergeCols - 1) / kMergeCols)),
-                     dim3(kMergeThreads), 0, stream, N, V, tiles_voc, pl.Npad, part_m, part_s1, part_s2, zt, hn, target, gamma, logp, p_sq, err_flag);
+  merge_variant(tiles_voc, [&](auto slices) {
+    hipLaunchKernelGGL(proxy_finalize_kernel<slices.value>, dim3((unsigned)((N + kMergeCols - 1) / kMergeCols)),
+                       dim3(kMergeCols * slices.value), 0, stream, N, V, tiles_voc, pl.Npad, part_m, part_s1, part_s2, zt,
+                       hn, target, gamma, logp, p_sq, err_flag);
+  });
   PSPO_LAUNCHED("proxy_finalize_kernel", stream);
   return PSPO_OK;
 }

@@ -1,6 +1,7 @@
 """GPU: merging the vocabulary-tile partials (384 rows each) of the loss and of the score proxy,
-where the slices of a merge (32 per token, 32 tokens per block) come out uneven: fewer tiles than
-slices, exactly as many, one more, several rounds; one token, and counts around a block.
+where the slices of a merge (1 per token for one tile, 4 up to 8 tiles, then 32; 32 tokens per block)
+come out uneven: fewer tiles than slices, exactly as many, one more, several rounds; one token, and
+counts around a block.
 
 Tolerances: a log-prob is z_o - M - log(sum), float32 sums of positive terms and logits of float32
 products, so about log2(V) * 2^-24 relative on the sum and 2^-24 |z| on the logits: 1e-5 absolute
@@ -15,7 +16,7 @@ from paper_2606_29758_amd import pspo, synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("V", [300, 384 * 31, 384 * 32, 384 * 32 + 1, 384 * 65 + 383])
+@pytest.mark.parametrize("V", [300, 384, 385, 384 * 4, 384 * 5, 384 * 8, 384 * 8 + 1, 384 * 31, 384 * 32, 384 * 32 + 1, 384 * 65 + 383])
 @pytest.mark.parametrize("N", [1, 31, 32, 65])
 def test_merge(N, V):
     print(f"[merge] N={N} V={V}", flush=True)
