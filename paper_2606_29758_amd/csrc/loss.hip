@@ -463,6 +463,16 @@ __global__ __launch_bounds__(256) void zero_targets_kernel(int N, const int32_t*
   }
 }
 
+// What a wave's lanes wrote to LDS before it, the others read after it, and nothing
+// read before it is overwritten: the hardware runs a wave's LDS accesses in order, and
+// the fences keep the compiler to that order (a barrier of the wave alone is none to
+// it; they emit no instruction).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // A wave's 192 x 128 part of a product written to rows of float32, one block of
 // 16 rows at a time through the wave's own LDS, so that each store (and, where the
 // rows are added to, each load, kAhead blocks ahead) moves 16 bytes per lane and
@@ -510,12 +520,12 @@ __device__ __forceinline__ void write_wave_rows(const AccTile& acc, int wave, fl
     for (int j = 0; j < kBlocksN; ++j)
 #pragma unroll
       for (int r = 0; r < kAccPerBlock; ++r) put[r * kLdsRowF + j * 16] = acc_get(acc, i, j, r);
-    __builtin_amdgcn_wave_barrier();   // (a wave's LDS accesses run in order)
+    wave_lds_fence();
     f32x4 x[kPieces];
 #pragma unroll
     for (int q = 0; q < kPieces; ++q)
       x[q] = *reinterpret_cast<const f32x4*>(get + q * 2 * kLdsRowF) + old[i % kAhead][q];
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_fence();
 #pragma unroll
     for (int q = 0; q < kPieces; ++q)
       if (at[i % kAhead][q] >= 0) *place(at[i % kAhead][q]) = x[q];
