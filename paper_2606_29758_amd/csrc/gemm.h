@@ -326,23 +326,34 @@ struct EpiSlab {
   }
 };
 
+// The tail of an XCD: its r tiles after the `full` positions of its whole rounds
+// (r <= 0: no tail), each in tail_parts(r, nk) K parts.
+struct TailTiles {
+  int full, r;
+};
+__host__ __device__ inline TailTiles tail_tiles(const TileGrid& tg, int x) {
+  const int full = tg.per_xcd / 32 * 32;
+  return {full, xcd_count(tg, x) - full};
+}
+// The work-group that computes part `part` of tail tile u (< r) of XCD x, and the
+// slab it leaves the part in; map_tail is the way back.
+__host__ __device__ inline int tail_slab(int x, int r, int u, int part) { return x + kNumXcd * (part * r + u); }
+
 // Tail launch: work-group x + 8 k (x the XCD, k < 64) takes part k / r of the
-// XCD's tail tile k % r, K steps [part nk / S, (part + 1) nk / S).  The tail
-// tiles are the positions after the XCD's whole rounds.  The tiles of one part lie
-// next to each other, so that an XCD's L2 serves the panels they share: the
+// XCD's tail tile k % r, K steps [part nk / S, (part + 1) nk / S).  The tiles of one
+// part lie next to each other, so that an XCD's L2 serves the panels they share: the
 // neighbours in the grouped order are up to 4 row tiles of a column tile, and with
 // the parts of a tile next to each other instead each of the 32 running
-// work-groups read its own row panel (2,048 tokens: 7,317 -> 7,198 us a call).  Returns false for work-groups
-// without a part.
+// work-groups read its own row panel (2,048 tokens: 7,317 -> 7,198 us a call).  Returns
+// false for work-groups without a part.
 __host__ __device__ inline bool map_tail(const TileGrid& tg, int bid, int nk, int& tm, int& tn, int& kb, int& ke) {
   const int x = bid % kNumXcd, k = bid / kNumXcd;
-  const int full = tg.per_xcd / 32 * 32;
-  const int r = xcd_count(tg, x) - full;
-  if (r <= 0 || k >= kTailSlots) return false;
-  const int parts = tail_parts(r, nk);
-  const int u = k % r, part = k / r;
+  const TailTiles t = tail_tiles(tg, x);
+  if (t.r <= 0 || k >= kTailSlots) return false;
+  const int parts = tail_parts(t.r, nk);
+  const int u = k % t.r, part = k / t.r;
   if (part >= parts) return false;
-  tile_at(tg, xcd_position(tg, x, full + u), 0, tm, tn);
+  tile_at(tg, xcd_position(tg, x, t.full + u), 0, tm, tn);
   kb = part * nk / parts;
   ke = (part + 1) * nk / parts;
   return true;

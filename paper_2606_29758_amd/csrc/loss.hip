@@ -910,7 +910,7 @@ __global__ __launch_bounds__(kFinThreads) void reduce_loss_kernel(int nblk, cons
 // The tail tiles of a product launched as whole rounds plus a K-split tail
 // (gemm_nt_kernel with kLaunchRounds, then kLaunchTail + EpiSlab): each tail
 // tile's K parts are summed in order from the slabs of its work-groups
-// x + 8 (p r + u) and handed to `out` four columns of a row at a time.  A thread
+// (tail_slab) and handed to `out` four columns of a row at a time.  A thread
 // sums one 16-byte piece, with up to kPartsAhead parts in flight: with a quarter
 // of the threads and a part at a time the latency of 32 parts took 43 us.
 // Grid (24 blocks of 16 rows, 8 XCDs x the tail tiles an XCD can have).
@@ -923,24 +923,23 @@ __global__ __launch_bounds__(kTailThreads) void tail_reduce_kernel(GemmShape g, 
   bounded_dims(g, M, N, K);
   const TileGrid tg = tile_grid(g.tiles_m, g.tiles_n, M, N);
   const int x = blockIdx.y % kNumXcd, u = blockIdx.y / kNumXcd;
-  const int full = tg.per_xcd / 32 * 32;
-  const int r = xcd_count(tg, x) - full;
-  if (u >= r) return;
-  const int parts = tail_parts(r, K / kTileK);
+  const TailTiles t = tail_tiles(tg, x);
+  if (u >= t.r) return;
+  const int parts = tail_parts(t.r, K / kTileK);
   int tm, tn;
-  tile_at(tg, xcd_position(tg, x, full + u), 0, tm, tn);
+  tile_at(tg, xcd_position(tg, x, t.full + u), 0, tm, tn);
   const int rb = blockIdx.x, tid = threadIdx.x;
   // the slab layout [24 blocks of 16 rows][256 columns][16]: thread tid takes
   // rows 4 (tid % 4) .. +3 of column tid / 4 of row block rb
   constexpr int64_t kSlabPieces = kTileM * kTileN / 4;
-  const f32x4* src = reinterpret_cast<const f32x4*>(slab) + (x + kNumXcd * u) * kSlabPieces +
-                     rb * (4 * kTileN) + tid;
+  const int slab0 = tail_slab(x, t.r, u, 0), to_next = tail_slab(x, t.r, u, 1) - slab0;   // parts lie evenly
+  const f32x4* src = reinterpret_cast<const f32x4*>(slab) + slab0 * kSlabPieces + rb * (4 * kTileN) + tid;
   f32x4 sum = {0.f, 0.f, 0.f, 0.f};
   for (int p = 0; p < parts; p += kPartsAhead) {
     f32x4 part[kPartsAhead];
 #pragma unroll
     for (int e = 0; e < kPartsAhead; ++e)   // (past the last part: it once more, not added)
-      part[e] = __builtin_nontemporal_load(src + (int64_t)min(p + e, parts - 1) * r * (kNumXcd * kSlabPieces));
+      part[e] = __builtin_nontemporal_load(src + (int64_t)min(p + e, parts - 1) * to_next * kSlabPieces);
 #pragma unroll
     for (int e = 0; e < kPartsAhead; ++e)
       if (p + e < parts) sum += part[e];

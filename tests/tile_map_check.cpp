@@ -34,7 +34,9 @@ static int check_spread() {
 }
 
 // whole launch, and whole rounds + K-split tail: every tile once, each tail
-// tile's K parts partition [0, nk), slabs unique and below 8 x kTailSlots
+// tile's K parts partition [0, nk); and the slabs the reduction reads (tail_slab of
+// every XCD, tail tile and part) are distinct, below 8 x kTailSlots, and those of the
+// work-groups that compute just these parts of these tiles, with none left over
 static int check_launches(int tiles_m, int tiles_n, int M, int N, int nk) {
   const int grid = (tiles_m * tiles_n + kNumXcd - 1) / kNumXcd * kNumXcd;
   const TileGrid tg = tile_grid(tiles_m, tiles_n, M, N);
@@ -66,6 +68,27 @@ static int check_launches(int tiles_m, int tiles_n, int M, int N, int nk) {
       pos = r.second;
     }
     if (pos != nk) return fail("K end", kv.first.first, kv.first.second, pos);
+  }
+  std::set<int> slabs;
+  for (int x = 0; x < kNumXcd; ++x) {
+    const TailTiles t = tail_tiles(tg, x);
+    const int parts = t.r > 0 ? tail_parts(t.r, nk) : 0;
+    for (int u = 0; u < t.r; ++u)
+      for (int p = 0; p < parts; ++p) {
+        const int bid = tail_slab(x, t.r, u, p);
+        if (bid != tail_slab(x, t.r, u, 0) + p * (tail_slab(x, t.r, u, 1) - tail_slab(x, t.r, u, 0)))
+          return fail("slabs of a tile's parts uneven", x, u, p);   // (the reduction's stride)
+        int tm0, tn0, tm, tn, kb, ke;
+        tile_at(tg, xcd_position(tg, x, t.full + u), 0, tm0, tn0);
+        if (bid < 0 || bid >= kNumXcd * kTailSlots || !slabs.insert(bid).second) return fail("slab", x, u, p);
+        if (!map_tail(tg, bid, nk, tm, tn, kb, ke) || tm != tm0 || tn != tn0) return fail("slab's tile", x, u, p);
+        if (kb != (int)((int64_t)p * nk / parts) || ke != (int)((int64_t)(p + 1) * nk / parts))
+          return fail("slab's part", x, u, p);
+      }
+  }
+  for (int bid = 0; bid < kNumXcd * kTailSlots; ++bid) {
+    int tm, tn, kb, ke;
+    if (map_tail(tg, bid, nk, tm, tn, kb, ke) && slabs.count(bid) == 0) return fail("slab nobody reads", bid, tiles_m, tiles_n);
   }
   int sum = 0;
   for (int x = 0; x < kNumXcd; ++x) {
