@@ -60,3 +60,37 @@ def ambiguous_clip(ref, eps_low, eps_high, band=1e-5):
     """Tokens whose ratio sits so close to a clip bound that float32 and float64 may disagree."""
     rho = ref["rho"]
     return (np.abs(rho - (1 + f32(eps_high))) < band) | (np.abs(rho - (1 - f32(eps_low))) < band)
+
+
+def loss_in(workspace_bytes, hidden, w_head, target, logp_old, weight, seq_id, advantage, N, eps_low, eps_high,
+            loss_scale, flags=0, d_w_head=None, want_logp=True):
+    """pspo_loss_fwd_bwd in a workspace of the given size, straight through the library: the
+    binding asks for the full size, the library also takes the smaller one of the chunked plan.
+    Returns the outputs and the vocabulary chunks that the backward ran in."""
+    import torch
+
+    from paper_2606_29758_amd import pspo
+    V, d = w_head.shape
+    new = lambda shape, dt=torch.float32: torch.empty(shape, dtype=dt, device="cuda")   # noqa: E731
+    out = dict(loss=new(1, torch.float64), d_hidden=new((N, d)), d_w_head=new((V, d)) if d_w_head is None else d_w_head,
+               logp_new=new(N) if want_logp else None, stats=new(5, torch.float64))
+    ws = new(workspace_bytes, torch.uint8)
+    lib, ptr = pspo.load(), (lambda x: None if x is None else x.data_ptr())
+    pspo.timing_start(256)
+    rc = lib.pspo_loss_fwd_bwd(*[ptr(x) for x in (hidden, w_head, target, logp_old, weight, seq_id, advantage)], N, d, V,
+                               advantage.shape[0], eps_low, eps_high, loss_scale, flags, ptr(out["loss"]),
+                               ptr(out["d_hidden"]), ptr(out["d_w_head"]), ptr(out["logp_new"]), ptr(out["stats"]), None,
+                               ptr(ws), workspace_bytes, torch.cuda.current_stream().cuda_stream)
+    chunks = pspo.timing_stop()["logit_grad"]["count"]
+    assert rc == 0, lib.pspo_last_error()
+    torch.cuda.synchronize()
+    return out, chunks
+
+
+def loss_chunked(step, pk, N, want_logp=True):
+    """A loss call of few tokens without the room for one vocabulary chunk: the chunked backward."""
+    from paper_2606_29758_amd import pspo
+    dw = step.dw
+    size = pspo.loss_workspace_bytes(N, dw.d, dw.V, 0) - 256
+    return loss_in(size, pk["hidden"], dw.w_head, pk["target"], pk["logp_old"], pk["weight"], pk["seq_id"], dw.advantage,
+                   N, dw.eps_low, dw.eps_high, dw.loss_scale, want_logp=want_logp)

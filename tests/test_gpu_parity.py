@@ -19,7 +19,7 @@ import torch
 from oracle import ppo_head as ohead
 from paper_2606_29758_amd import pipeline, pspo, synth
 
-from parity_util import (GRAD_REL_L2, LOGP_ATOL, LOSS_RTOL, ambiguous_clip, f32, logp_old_for,
+from parity_util import (GRAD_REL_L2, LOGP_ATOL, LOSS_RTOL, ambiguous_clip, f32, logp_old_for, loss_chunked,
                          oracle_logp_old, oracle_loss, oracle_sample_pack, rel_l2)
 
 pytestmark = pytest.mark.gpu
@@ -32,7 +32,8 @@ MINI = {
     "mini7b": synth.custom("mini7b", "qwen7b", P=2, K=2, length_law=("uniform", 150, 420), data_seed=31),
     "mini1p5b": synth.custom("mini1p5b", "qwen1.5b", P=2, K=3, length_law=("uniform", 60, 300), data_seed=21),
     # odd shapes: a vocabulary that is no multiple of 32 (2.6 tiles of 384, one chunk) with a width
-    # of 6 K steps, and one of three chunks whose last ends in a partial tile (7B width)
+    # of 6 K steps, and one whose last tile is partial (7B width; three chunks in a workspace
+    # without the room for one)
     "odd_small": synth.custom("odd_small", "tiny", d=192, V=1000, P=2, K=3, length_law=("uniform", 20, 90),
                               data_seed=41),
     "odd_chunks": synth.custom("odd_chunks", "qwen7b", V=130003, P=2, K=3, length_law=("uniform", 60, 160),
@@ -126,6 +127,25 @@ def _compare_loss(out, ref):
     assert e_h <= GRAD_REL_L2 and e_w <= GRAD_REL_L2
 
 
+# the vocabulary chunks of the large vocabularies where one chunk has no room
+CHUNKS = 3
+
+
+def _compare_chunked(step, out, ref, want_logp=True):
+    """The same call by the chunked backward (these calls have at most 768 tokens, which run in one
+    chunk given the room), against the oracle too."""
+    if step.dw.V < 100000:
+        return     # one chunk either way
+    assert out["N"] <= 768
+    chunked, ran = loss_chunked(step, out["pack"], out["N"], want_logp)
+    assert ran == CHUNKS
+    if want_logp:
+        _compare_loss(chunked, ref)
+    assert torch.equal(chunked["loss"], out["loss"])
+    for k in ("d_hidden", "d_w_head"):
+        assert rel_l2(_to_np(chunked[k]), ref[k if k == "d_hidden" else "d_w"]) <= GRAD_REL_L2
+
+
 @pytest.mark.parametrize("name,seed", [("tiny", 0), ("tiny", 1), ("tiny", 123456789), ("tiny_full", 0),
                                        ("mini1p5b", 0), ("mini7b", 3), ("odd_small", 0), ("odd_chunks", 2),
                                        ("odd_d", 1)])
@@ -133,13 +153,15 @@ def test_loss_parity(name, seed):
     wl, lp = _workload(name)
     cfg = wl.cfg
     dw = pipeline.upload(wl, lp)
-    out = pipeline.Step(dw)(seed=seed)
+    step = pipeline.Step(dw)
+    out = step(seed=seed)
     torch.cuda.synchronize()
     H, pk = oracle_sample_pack(wl, lp, seed)
     _check_pack(out, H, pk)
     ref = oracle_loss(wl, pk)
     assert not ambiguous_clip(ref, cfg.eps_low, cfg.eps_high).any()
     _compare_loss(out, ref)
+    _compare_chunked(step, out, ref)
     # the clip mask and degenerate groups agree exactly
     A = wl.advantage[pk["seq_id"]]
     st = _to_np(out["stats"])
@@ -161,13 +183,15 @@ def test_loss_variants(name, eps_low, eps_high, adv_norm):
     cfg = dataclasses.replace(wl.cfg, eps_low=eps_low, eps_high=eps_high, adv_norm=adv_norm)
     adv = synth.make_workload(cfg, with_matrices=False).advantage
     wl1 = synth.Workload(**{**wl.__dict__, "cfg": cfg, "advantage": adv})
-    out = pipeline.Step(pipeline.upload(wl1, lp))(seed=5)
+    step = pipeline.Step(pipeline.upload(wl1, lp))
+    out = step(seed=5)
     torch.cuda.synchronize()
     H, pk = oracle_sample_pack(wl1, lp, 5)
     _check_pack(out, H, pk)
     ref = oracle_loss(wl1, pk)
     assert not ambiguous_clip(ref, eps_low, eps_high).any()
     _compare_loss(out, ref)
+    _compare_chunked(step, out, ref)
     A = adv[pk["seq_id"]]
     st = _to_np(out["stats"])
     assert int(st[1]) == int(np.sum((A != 0) & (ref["mu"] == 0)))
@@ -206,10 +230,11 @@ def test_kept_logits_match_recompute(name, want_logp):
     """With PSPO_KEEP_LOGITS the forward keeps the first vocabulary chunk's logits (as fp16
     offsets from each tile's per-column maximum) and the backward turns them into that
     chunk's logit gradient without a recomputing product.  The forward outputs (loss,
-    log-probs, stats) are bitwise those of the default path, which recomputes every chunk;
-    the gradients differ only by the fp16 rounding of the kept offsets, and both match the
-    oracle.  tiny has one chunk (the whole padded vocabulary); the 7B and 1.5B widths have
-    several."""
+    log-probs, stats) are bitwise those of the default path, which recomputes every logit (at
+    these token counts in one chunk, and with less room chunk by chunk, as the kept path runs);
+    the gradients differ only by the fp16 rounding of the kept offsets and the order of float32
+    sums, and all match the oracle.  tiny has one chunk (the whole padded vocabulary); the 7B
+    and 1.5B widths have three."""
     wl, lp = _workload(name)
     step = pipeline.Step(pipeline.upload(wl, lp))
     pk = step.sample_and_pack(seed=11)
@@ -233,6 +258,7 @@ def test_kept_logits_match_recompute(name, want_logp):
     for out in (ka, b):
         assert rel_l2(_to_np(out["d_hidden"]), ref["d_hidden"]) <= GRAD_REL_L2
         assert rel_l2(_to_np(out["d_w_head"]), ref["d_w"]) <= GRAD_REL_L2
+    _compare_chunked(step, dict(ka, N=N, pack=pk), ref, want_logp)
 
 
 def _scaled_w(wl, k):
@@ -247,8 +273,8 @@ def _scaled_w(wl, k):
 def test_large_logits(name, k, seed):
     """Logits of standard deviation ~20-30 (W scaled by 2^k): peaked softmax rows, targets
     dozens of nats below the tile maxima, kept fp16 offsets far into their coarse range.
-    The default path (every chunk recomputed) and the kept-chunk path both match the oracle,
-    agree with each other to ~1e-4 on the gradients, and bitwise on loss and log-probs."""
+    The default path (every logit recomputed, in one chunk and in three) and the kept-chunk path
+    all match the oracle, agree with each other to ~1e-4 on the gradients, and bitwise on loss and log-probs."""
     wl, _ = _workload(name)
     wl, lp = _scaled_w(wl, k)
     cfg = wl.cfg
@@ -261,6 +287,7 @@ def test_large_logits(name, k, seed):
     assert not ambiguous_clip(ref, cfg.eps_low, cfg.eps_high).any()
     assert np.median(ref["logp_new"]) < -10.0   # the regime this test is for
     _compare_loss(ka, ref)
+    _compare_chunked(step, dict(ka, N=out["N"], pack=out["pack"]), ref)
     pkg = step.sample_and_pack(seed)
     N = int(pkg["n_tokens"].item())
     b = step.loss(pkg, N, flags=pspo.PSPO_KEEP_LOGITS)
