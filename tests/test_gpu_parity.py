@@ -477,10 +477,12 @@ def test_nonfinite_flag():
 
 
 def _chunk_rows(d, V):
-    """The backward's vocabulary chunk as the header documents it:
-    Vc = 384 * 256 / gcd(ceil(d / 256), 256) rows, or the whole padded vocabulary."""
+    """The backward's vocabulary chunk of calls past 768 tokens, as the header documents it: the
+    padded vocabulary split evenly, to whole tiles of 384, by Vb = 384 * 256 / gcd(ceil(d / 256), 256)."""
     import math
-    return min(384 * 256 // math.gcd(-(-d // 256), 256), -(-V // 384) * 384)
+    Vb, Vpad = 384 * 256 // math.gcd(-(-d // 256), 256), -(-V // 384) * 384
+    n = max(1, Vpad // Vb + (1 if Vpad >= Vb and 4 * (Vpad % Vb) > Vb else 0))
+    return -(-(-(-Vpad // n)) // 384) * 384
 
 
 def _dw_rows(V, Vc, target, k_random=24, seed=19):
