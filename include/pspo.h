@@ -186,19 +186,22 @@ size_t pspo_loss_workspace_bytes(int32_t N, int32_t d, int32_t V, uint32_t flags
  *   d_hidden[i] = G_i W,   d_w_head = sum_i G_i^T h_i.
  * The [N, V] logits are never written to memory: the forward keeps per-token
  * softmax statistics only, and the backward recomputes the logit tiles one
- * vocabulary chunk at a time.  G is applied in two parts: -delta_i p_i as one
- * chunk of bf16 values at a time (in two layouts) through the matrix cores,
- * and the one-hot part delta_i e_{o_i} in float32 (d_hidden[i] += delta_i W[o_i];
- * d_w_head[v] += sum_{i : o_i = v} delta_i h_i, each row's terms summed in token
- * order), so the largest entry of each row of G is never rounded to bf16.
+ * vocabulary chunk at a time.  G is applied in two parts: the entries -delta_i p_{i,v},
+ * v != o_i, as one chunk of bf16 values at a time (in two layouts) through the
+ * matrix cores, and the target entries g_i = delta_i (1 - p_i(o_i)) in float32
+ * (d_hidden[i] += g_i W[o_i]; d_w_head[v] += sum_{i : o_i = v} g_i h_i), so that
+ * they are never rounded to bf16.  Each row of the latter is summed in spans of 32
+ * tokens of the list sorted by target and position, whose sums are then added in
+ * order: the grouping depends on where an id falls in that list.
  * The chunk width is about Vb = 384 * 256 / gcd(ceil(d / 256), 256) rows: the
  * vocabulary (padded to 384) is split evenly into floor(V / Vb) chunks, or one
  * more when the remainder exceeds Vb / 4 (one chunk if V < Vb), each a
  * multiple of 384 rows; three chunks of 50688 rows at d = 3584, V = 152064.
  * Calls of at most 768 tokens without kept logits use one chunk (the size that
  * pspo_loss_workspace_bytes() gives for any larger N covers that; in a workspace
- * that only holds the chunks they run chunked).  Every result is deterministic
- * (no floating-point atomics).
+ * that only holds the chunks they run chunked, and the gradients' last bits are
+ * those of the chunked sums).  Every result is deterministic (no floating-point
+ * atomics): it depends on the arguments and on which of the two the workspace holds.
  *
  *  hidden     device, bf16 bits [N, d] row-major (packed prefix tokens).
  *  w_head     device, bf16 bits [V, d] row-major.

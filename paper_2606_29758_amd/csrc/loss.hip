@@ -31,9 +31,10 @@
 //      memory-bound conversion replaces that chunk's recompute;
 //   6. the target entries in float32, g_i = G_{i,o_i} = delta_i (1 - p_i(o_i))
 //      = -delta_i expm1(l_i): dH_i += g_i W[o_i], and
-//      dW[v] += sum_{i : o_i = v} g_i h_i with each row's terms summed in token
-//      order (the backward tokens sorted by target and position; no
-//      floating-point atomics).  The target entry is the largest of its row
+//      dW[v] += sum_{i : o_i = v} g_i h_i, the backward tokens sorted by target
+//      and position and summed in spans of 32 of that list, whose sums of one id are
+//      then added in order (no floating-point atomics: the grouping depends on the
+//      tokens' targets alone).  The target entry is the largest of its row
 //      when the softmax is flat and the result of a cancellation when it is
 //      peaked; carried in float32 it is rounded neither to 8 bits nor after a
 //      cancellation.
@@ -1314,11 +1315,15 @@ Plan make_plan(int64_t N, int64_t d, int64_t V, bool keep, bool one_chunk) {
 
 // Calls of few tokens (one token block of 768) run the backward in one chunk when
 // the workspace has room for it: a chunk of theirs leaves most CUs idle (132 tiles
-// for 256 CUs at 200 tokens and V = 152064), and each costs its launches: 2,380 us
-// a call there in three chunks, 2,131 in one.
+// for 256 CUs at 200 tokens and V = 152064), and each costs its launches.  us a call,
+// chunked / one chunk: d = 3584, V = 152064 2,192 / 1,954 at 1 token, 2,372 / 2,124 at
+// 200, 3,208 / 2,847 at 500, 3,590 / 3,340 at 768; d = 1536, V = 152064 1,345 / 1,122
+// at 200, 1,888 / 1,670 at 768; d = 4096, V = 128256 (narrow chunks) 4,758 / 2,121 and
+// 5,699 / 3,238; never slower from d = 512 to 8192 and V = 32000 to 152064.
 // The logit gradient of the whole vocabulary then takes 2 x 768 x V x 2 bytes
-// (467 MB, next to 2.2 GB of operand copies of W, at d = 3584, V = 152064).  With
-// kept logits the plan stays chunked (the first chunk's are kept).
+// (467 MB, next to 2.2 GB of operand copies of W, at d = 3584, V = 152064, where a
+// chunk's takes 156).  With kept logits the plan stays chunked (the first chunk's are
+// kept).
 Plan choose_plan(int64_t N, int64_t d, int64_t V, bool keep, size_t workspace_bytes) {
   if (!keep && N <= kTileLcm) {
     const Plan p = make_plan(N, d, V, keep, true);
