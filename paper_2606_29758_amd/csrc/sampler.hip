@@ -167,43 +167,29 @@ __global__ void pack_fill_kernel(const int32_t* __restrict__ cu_seqlens, const i
   }
 }
 
-// Copies the kept hidden rows, one wave per row, 16 bytes per lane.  When the rows
-// read and written together exceed the memory-side cache (256 MB), a row's next
-// kPieces loads go out before their stores and both go past the caches, which could not
-// serve the copy's reader: sampling and packing 32 completions of up to 16,384 tokens,
-// d = 3584 (2.8 GB moved), one load at a time through the caches 688 us, so 625 us,
-// 4.5 TB/s.  A smaller copy goes through the caches, from which the next call reads
-// it (past them / through them: 5,676 rows of d = 3584 23.3 / 20.8 us, 56,843 of
-// d = 1024 51.2 / 44.8, 90,763 of d = 512 138.8 / 126.6; above the line 90,083 of
-// d = 768 164.4 / 195.2, 139,930 of d = 520 72.8 / 79.5), and so do rows of fewer
-// pieces than lanes, which the caches join to whole lines.  kLarge: the capacity
-// leaves it open which of the two it is; otherwise through the caches.
-constexpr int64_t kMemorySideBytes = int64_t(256) << 20;
-__host__ __device__ inline bool pack_passes(int64_t rows, int32_t vec_per_row) {
-  return vec_per_row >= 64 && rows * vec_per_row * (2 * (int64_t)sizeof(u32x4)) > kMemorySideBytes;
-}
-template <bool kLarge>
+// Copies the kept hidden rows, one wave per row, 16 bytes per lane.  kPast: a row's
+// next kPieces loads go out before their stores and both go past the caches (sampling
+// and packing 32 completions of up to 16,384 tokens, d = 3584, 2.8 GB moved: one load
+// at a time through the caches 688 us, so 625 us, 4.5 TB/s); otherwise through the
+// caches, from which the next call reads a small copy, and which join short rows to
+// whole lines (pack_past).
+template <bool kPast>
 __global__ __launch_bounds__(256) void pack_hidden_kernel(const int32_t* __restrict__ cu_seqlens,
                                                           const int32_t* __restrict__ full_off, int32_t capacity,
                                                           const u32x4* __restrict__ hidden_full,
                                                           u32x4* __restrict__ hidden, int32_t vec_per_row) {
-  constexpr int kPieces = 8;
   const int r = blockIdx.y;
   const int32_t c0 = cu_seqlens[r], H = cu_seqlens[r + 1] - c0;
+  const int32_t f0 = full_off[r];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int waves = blockDim.x >> 6;
-  bool past = false;
-  if constexpr (kLarge) {
-    if (blockIdx.x * waves >= H) return;   // (most blocks, where completions are short)
-    past = pack_passes(min(cu_seqlens[gridDim.y], capacity), vec_per_row);
-  }
-  const int32_t f0 = full_off[r];
   for (int j = blockIdx.x * waves + wave; j < H; j += gridDim.x * waves) {
     const int64_t i = (int64_t)c0 + j;
     if (i >= capacity) break;
     const u32x4* src = hidden_full + (int64_t)(f0 + j) * vec_per_row;
     u32x4* dst = hidden + i * vec_per_row;
-    if (past) {
+    if constexpr (kPast) {
+      constexpr int kPieces = 8;
       for (int b = lane; b < vec_per_row; b += 64 * kPieces) {
         u32x4 x[kPieces];
 #pragma unroll
@@ -217,6 +203,17 @@ __global__ __launch_bounds__(256) void pack_hidden_kernel(const int32_t* __restr
       for (int b = lane; b < vec_per_row; b += 64) dst[b] = src[b];
     }
   }
+}
+
+// Past the caches: rows of more pieces than lanes, where the capacity's rows read and
+// written come to 160 MB (the kept ones then to some 96).  us for sampling and packing,
+// some 60 of them host time, through the caches / past them, on rows new to the GPU:
+// 2,400 rows of d = 3584 (capacity 63 MB) 66.4 / 71.9, 15,000 of d = 1536 (172 MB)
+// 85.2 / 85.4, of d = 2048 (229 MB) 97.3 / 93.3, 55,000 of d = 2048 200 / 186, of
+// d = 128 73.0 / 79.3, of d = 512 91.3 / 94.0.  On rows that the caches hold already
+// (without the host time): 5,676 of d = 3584 (137 MB) 20.7 / 23.3.
+inline bool pack_past(int64_t capacity, int32_t vec_per_row) {
+  return vec_per_row > 64 && capacity * vec_per_row * (2 * (int64_t)sizeof(u32x4)) > int64_t(160) << 20;
 }
 
 }  // namespace
@@ -286,7 +283,7 @@ int pspo_pack_prefixes(const int32_t* cutoffs, const int32_t* lengths, const dou
                      capacity, target_full, logp_old_full, src_row, seq_id, weight, target, logp_old);
   PSPO_LAUNCHED("pack_fill_kernel", stream);
   if (hidden_full) {
-    hipLaunchKernelGGL(pack_passes(capacity, d / 8) ? pack_hidden_kernel<true> : pack_hidden_kernel<false>, dim3(64, R),
+    hipLaunchKernelGGL(pack_past(capacity, d / 8) ? pack_hidden_kernel<true> : pack_hidden_kernel<false>, dim3(64, R),
                        dim3(256), 0, stream, cu_seqlens, full_off, capacity, reinterpret_cast<const u32x4*>(hidden_full),
                        reinterpret_cast<u32x4*>(hidden), d / 8);
     PSPO_LAUNCHED("pack_hidden_kernel", stream);

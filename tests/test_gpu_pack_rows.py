@@ -1,7 +1,7 @@
-"""GPU: the gather of the kept hidden rows on both sides of its line (rows read and written together
-past 256 MB, in rows of at least 64 16-byte pieces), with rows that end inside a round of 8 x 64
-pieces, completions that keep nothing, everything, or a prefix, and a capacity at, below and above the
-kept count (which leaves the line to the device).
+"""GPU: the gather of the kept hidden rows on both sides of its line (the capacity's rows read and
+written past 160 MB, in rows of more than 64 16-byte pieces), with rows that end inside a round of
+8 x 64 pieces, completions that keep nothing, everything, or a prefix, and a capacity at, below and
+above the kept count.
 The bytes are those of the rows.
 """
 import numpy as np
@@ -12,8 +12,8 @@ from paper_2606_29758_amd import pspo
 
 pytestmark = pytest.mark.gpu
 
-# d, kept rows: 131,072 rows of 64 pieces are exactly 256 MB
-CASES = [(8, 5000), (504, 140000), (512, 131072), (512, 131073), (520, 129500), (3592, 2000), (3592, 19000), (4104, 16500)]
+# d, kept rows: 81,920 rows of 64 pieces would be 160 MB; 10,922 of 480 pieces just are not, 10,923 are
+CASES = [(8, 5000), (512, 90000), (520, 80000), (520, 81000), (3592, 2000), (3592, 13000), (3840, 10922), (3840, 10923), (4104, 11000)]
 
 
 @pytest.mark.parametrize("d,kept", CASES)
