@@ -359,8 +359,8 @@ int pspo_design_cutoffs(const double* w, const int64_t* xi_off, int32_t P, int64
  * For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * survival tables as pspo_design_cutoffs, bitwise, with no workspace argument.
- * The PAV block stack lives in a static device array of 8 MiB that the library
- * holds on each GPU it runs on until the process ends, so total_T <= 2^19
+ * The blocks of prompts too long for LDS live in a static device array of 8 MiB that
+ * the library holds on each GPU it runs on until the process ends, so total_T <= 2^19
  * (524288 steps); a larger total_T returns PSPO_ERR_UNSUPPORTED before
  * anything is enqueued.  The call allocates and frees nothing.  Every call on
  * one GPU shares that GPU's array: calls that overlap on one GPU (concurrent

@@ -145,11 +145,10 @@ def test_computing_xi_end_to_end():
 
 @pytest.mark.parametrize("variant", [cd.OPTIMIZED, cd.HEURISTIC])
 def test_design_cutoffs_lds_and_global_paths(variant):
-    """Prompt horizons on both sides of the solve's two LDS limits (its weights and block
-    stack in the 160 KB of LDS up to T = 8192, the weights alone up to T = 20480, both in
-    device memory beyond), in one call, against the oracle; the no-allocation entry point
-    gives the same bits."""
-    T = np.array([100, 8191, 8192, 8193, 20480, 20481, 30000], dtype=np.int64)
+    """Prompt horizons on both sides of the solve's LDS limit (its blocks of steps in LDS up to
+    T = 13040, in device memory beyond) and well past it, in one call, against the oracle; the
+    no-allocation entry point gives the same bits."""
+    T = np.array([100, 8191, 8192, 8193, 13039, 13040, 13041, 20480, 20481, 30000], dtype=np.int64)
     xi_off = np.concatenate([[0], np.cumsum(T)]).astype(np.int64)
     P, total = len(T), int(xi_off[-1])
     w = _random_weights(xi_off, 17)

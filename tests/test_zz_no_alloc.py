@@ -1,10 +1,11 @@
 """GPU: the no-allocation design entry point against the one that takes a workspace.
 
-pspo_design_cutoffs_noalloc runs the same solve with its block stack in the
-library's static device scratch.  Two calls in a row, the second on a smaller
-input (fewer prompts and steps, so stale entries of the first call sit in the
-scratch), each bitwise equal to pspo_design_cutoffs on the same weights, and
-within 1e-12 of the float64 oracle.
+pspo_design_cutoffs_noalloc runs the same solve with the blocks of the prompts
+past the LDS limit (13040 steps) in the library's static device scratch.  Calls in
+a row, the second of each pair on a smaller input: two within the limit, and two
+past it, where stale entries of the first call sit in the scratch; each bitwise
+equal to pspo_design_cutoffs on the same weights, and within 1e-12 of the float64
+oracle.
 """
 import numpy as np
 import pytest
@@ -30,7 +31,7 @@ def test_noalloc_matches_workspace_entry(variant):
     assert torch.cuda.is_available(), "GPU tests need an MI355X"
     pspo.load()
     dev = "cuda"
-    for seed, P, T_max, budget in ((1, 12, 3000, 96.0), (2, 3, 700, 40.0)):   # the second call is smaller
+    for seed, P, T_max, budget in ((1, 12, 3000, 96.0), (2, 3, 700, 40.0), (3, 4, 60000, 2000.0), (4, 2, 27000, 800.0)):
         w, off = _case(seed, P, T_max)
         total = int(off[-1])
         tw = torch.from_numpy(w).to(dev)
